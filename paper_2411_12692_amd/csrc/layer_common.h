@@ -133,12 +133,12 @@ __device__ inline void poison_tile(float* y, int b, int d, int tile, int lane) {
 }
 
 // Dot products of a row held as NU 16-byte units per lane (unit lane + 64 j)
-// with the BM tokens in LDS (token t at xs[t * NU * 64], a compile-time
+// with the BM tokens in LDS (token t at xs[t * XP], a compile-time
 // stride, so that the tokens of a unit are read with immediate offsets from
 // one address); wave-uniform results.
 // Units past the row's end (u >= U) hold a repeat of its last unit and are
 // left out with a select, not a branch.
-template <int BM, int NU>
+template <int BM, int NU, int XP = NU * kWave>
 __device__ inline void row_dots(const u32x4 (&v)[NU], const u32x4* xs, int U, int lane, float (&out)[BM]) {
   float acc[BM];
 #pragma unroll
@@ -149,7 +149,7 @@ __device__ inline void row_dots(const u32x4 (&v)[NU], const u32x4* xs, int U, in
     const int uc = min(u, U - 1);
 #pragma unroll
     for (int t = 0; t < BM; ++t) {
-      const float s = dot8(v[j], xs[t * (NU * kWave) + uc], acc[t]);
+      const float s = dot8(v[j], xs[t * XP + uc], acc[t]);
       acc[t] = u < U ? s : acc[t];
     }
   }

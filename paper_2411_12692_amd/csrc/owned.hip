@@ -117,6 +117,7 @@ constexpr int kMPitch = kTile * 2 + 32;   // bytes per row of a chunk in LDS (pa
 constexpr int kMTok = 16;                 // tokens of the MFMA (b <= 8 used)
 static_assert(kMRows == 4 * kOW, "each wave stages 4 rows of a chunk (16 lanes per row)");
 static_assert(kTile == 4 * 16 * kOW, "four 16-column blocks per wave");
+constexpr int kUpRows = 4;                // INT8 gate/up on the matrix cores: rows a wave takes at a time
 template <int BM>
 struct MfmaLds {
   unsigned char rows[kMRows * kMPitch];  // the chunk's pieces, row-major
@@ -155,10 +156,14 @@ struct OwnedArgs {
 template <int BM, int NU>
 struct OwnedLds {
   static constexpr int kUnits = NU * kWave;
+  // LDS stride of a token in 16-byte units: with 3-8 tokens (INT8 gate/up on
+  // the matrix cores) the same units of 4 tokens are read together, so 4 units
+  // of padding spread the tokens over the banks
+  static constexpr int kStride = kUnits + (BM >= 4 ? 4 : 0);
   static constexpr int kFold = kOW / BM;  // per-wave partial tiles held at once in the fold
   // tokens (fp16); once the gate/up work is done, the per-wave partial tiles
   union {
-    u32x4 xs[BM * kUnits];
+    u32x4 xs[BM * kStride];
     float dpart[kFold][BM][kTile];
     unsigned char mf_raw[BM >= 4 ? sizeof(MfmaLds<BM>) : 16];  // the down-projection on the matrix cores
   };
@@ -254,9 +259,9 @@ __device__ inline int census_part(const uint64_t* pub, int P, int t, int nt, uin
 }
 
 // Dot products of two rows held as NU 16-byte units per lane (unit lane +
-// 64 j) with the BM tokens in LDS (token t at xs[t * NU * 64]); each token
+// 64 j) with the BM tokens in LDS (token t at xs[t * XP]); each token
 // unit is read once for both rows.  Wave-uniform results.
-template <int BM, int NU>
+template <int BM, int NU, int XP>
 __device__ inline void row_dots2(const u32x4 (&v)[NU], const u32x4 (&w)[NU], const u32x4* xs, int U, int lane,
                                  float (&o1)[BM], float (&o2)[BM]) {
   float a1[BM], a2[BM];
@@ -268,7 +273,7 @@ __device__ inline void row_dots2(const u32x4 (&v)[NU], const u32x4 (&w)[NU], con
     const int uc = min(u, U - 1);
 #pragma unroll
     for (int t = 0; t < BM; ++t) {
-      const u32x4 xv = xs[t * (NU * kWave) + uc];
+      const u32x4 xv = xs[t * XP + uc];
       const float s1 = dot8(v[j], xv, a1[t]);
       const float s2 = dot8(w[j], xv, a2[t]);
       a1[t] = u < U ? s1 : a1[t];
@@ -287,17 +292,17 @@ __device__ inline void row_dots2(const u32x4 (&v)[NU], const u32x4 (&w)[NU], con
 
 // The 16 INT8 values of a 16-byte unit as 16 fp16 values (two 16-byte
 // vectors), exactly: each byte, offset by 128, becomes the low mantissa
-// byte of the fp16 value 1024 + (q + 128), from which 1152 is subtracted
-// (every value on the way is an integer below 2048).
-__device__ inline uint32_t i8_pair(uint32_t biased) {
-  return __builtin_bit_cast(uint32_t, as_h2(biased | 0x64006400u) - f16x2{(_Float16)1152.0f, (_Float16)1152.0f});
+// byte of the fp16 value 1024 + (q + 128) (one byte permute per pair), from
+// which 1152 is subtracted (every value on the way is an integer below 2048).
+__device__ inline uint32_t i8_pair(uint32_t biased, uint32_t sel) {
+  const uint32_t v = __builtin_amdgcn_perm(0x64646464u, biased, sel);
+  return __builtin_bit_cast(uint32_t, as_h2(v) - f16x2{(_Float16)1152.0f, (_Float16)1152.0f});
 }
 __device__ inline void i8_to_h16(u32x4 v, u32x4& lo, u32x4& hi) {
+  constexpr uint32_t k01 = 0x04010400u, k23 = 0x04030402u;  // bytes 0, 1 (2, 3) under the exponent byte 0x64
   const uint32_t a = v.x ^ 0x80808080u, b = v.y ^ 0x80808080u, c = v.z ^ 0x80808080u, e = v.w ^ 0x80808080u;
-  auto p01 = [](uint32_t t) { return i8_pair((t & 0xffu) | ((t & 0xff00u) << 8)); };
-  auto p23 = [](uint32_t t) { return i8_pair(((t >> 16) & 0xffu) | ((t >> 8) & 0xff0000u)); };
-  lo = u32x4{p01(a), p23(a), p01(b), p23(b)};
-  hi = u32x4{p01(c), p23(c), p01(e), p23(e)};
+  lo = u32x4{i8_pair(a, k01), i8_pair(a, k23), i8_pair(b, k01), i8_pair(b, k23)};
+  hi = u32x4{i8_pair(c, k01), i8_pair(c, k23), i8_pair(e, k01), i8_pair(e, k23)};
 }
 
 // Dot products of one or two INT8 rows held as (NU + 1) / 2 16-byte units
@@ -327,7 +332,6 @@ __device__ inline void row_dots_i8(const u32x4 (&v)[(NU + 1) / 2], const u32x4 (
         a2[t] = u < U8 ? s2 : a2[t];
       }
     }
-    if constexpr (BM >= 4) __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int t = 0; t < BM; ++t) {
@@ -444,6 +448,8 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   // flag
   constexpr bool block_mode = MODE == kModeBlock;
   constexpr bool kI8 = MODE == kModeInt8;
+  constexpr bool kMfma = BM >= 4;         // 3-8 tokens: the down-projection on the matrix cores
+  constexpr bool kMfmaUp = kMfma && kI8;  // and, with INT8 weights, gate/up
   if (!block_mode && owns_tile && wv == kTileWave) {
     const int half_cols = min(kTile, d - blk * kTile) / 2;
     for (int t = 0; t < b; ++t) {
@@ -466,8 +472,8 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       htile[1] = hv4[2 * tunit + 1];
     }
   }
-  // token t's unit u at xs[t * XS + u] (XS = NU * 64 >= U)
-  constexpr int XS = OwnedLds<BM, NU>::kUnits;
+  // token t's unit u at xs[t * XP + u], u < XS (XS = NU * 64 >= U)
+  constexpr int XS = OwnedLds<BM, NU>::kUnits, XP = OwnedLds<BM, NU>::kStride;
   // decoder-block mode: h and norm_w as 16-byte vectors; each thread's
   // units (two at most) are kept in registers from the sums of squares to
   // the scaling, which runs once the counts are done.  The units go to the
@@ -528,7 +534,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
           xv.z = pack_h2((q.x * rt) * wq.x, (q.y * rt) * wq.y);
           xv.w = pack_h2((q.z * rt) * wq.z, (q.w * rt) * wq.w);
         }
-        L.xs[i] = xv;
+        L.xs[t * XP + u] = xv;
       }
     }
   };
@@ -568,7 +574,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
             xv.z = pack_h2((q.x * rt) * wq.x, (q.y * rt) * wq.y);
             xv.w = pack_h2((q.z * rt) * wq.z, (q.w * rt) * wq.w);
           }
-          L.xs[t * XS + u] = xv;
+          L.xs[t * XP + u] = xv;
         }
       }
     }
@@ -604,9 +610,9 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       for (int j = 0; j < JX; ++j) {
         const int base = wv * kWave + j * kOT;  // the wave's first unit (wave-uniform)
         if (base < BM * XS) {
-          const int i = base + lane, t = i / XS, u = i - t * XS;
-          __builtin_amdgcn_global_load_lds(xg + min(t * U + u, nx - 1),
-                                           (__attribute__((address_space(3))) void*)(&L.xs[base]), 16, 0, 0);
+          const int t = base / XS, u0 = base - t * XS;
+          __builtin_amdgcn_global_load_lds(xg + min(t * U + u0 + lane, nx - 1),
+                                           (__attribute__((address_space(3))) void*)(&L.xs[t * XP + u0]), 16, 0, 0);
         }
       }
       if (tid == 0) {
@@ -619,7 +625,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
 #pragma unroll
       for (int j = 0; j < JX; ++j) {
         const int i = tid + j * kOT, t = i / XS, u = i - t * XS;
-        if (i < BM * XS && !(t < b && u < U)) L.xs[i] = u32x4{0, 0, 0, 0};
+        if (i < BM * XS && !(t < b && u < U)) L.xs[t * XP + u] = u32x4{0, 0, 0, 0};
       }
     } else {
       u32x4 xv[JX];
@@ -637,7 +643,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
 #pragma unroll
       for (int j = 0; j < JX; ++j) {
         const int i = tid + j * kOT, t = i / XS, u = i - t * XS;
-        if (i < BM * XS) L.xs[i] = (t < b && u < U) ? xv[j] : u32x4{0, 0, 0, 0};
+        if (i < BM * XS) L.xs[t * XP + u] = (t < b && u < U) ? xv[j] : u32x4{0, 0, 0, 0};
       }
     }
   } else {
@@ -740,7 +746,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     if (predict) {
       for (int i = tid; i < BM * W; i += kOT) {  // tokens b..BM-1 are zero
         const int t = i / W, w = i - t * W;
-        L.xw[i] = sign_word(&L.xs[t * OwnedLds<BM, NU>::kUnits + 4 * w]);
+        L.xw[i] = sign_word(&L.xs[t * XP + 4 * w]);
       }
     }
     __syncthreads();
@@ -921,7 +927,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     const int lo = (n * m) / T, hi = (n * (m + 1)) / T;  // this member's gate/up positions
     const int dN = n;                                     // the down item's positions
     if (tid == 0) {
-      L.gpos = lo + kOW;
+      L.gpos = lo + (kMfmaUp ? kUpRows : 1) * kOW;
       L.dpos = 0;
       L.issued = 0;
       L.wsum[0] = 0;
@@ -936,122 +942,290 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // token's ReLU output is positive.  Each wave works through its rows on
     // its own (no block barrier) and publishes h3 per row and token.
     int n_up = 0;
-    // one token: a wave announces (LDS counter) that its first row's
-    // requests are out, so that the waves without a row can queue their
-    // W_down^T pieces behind them
-    bool first = BM == 1;
-    auto announce = [&]() {
-      if constexpr (BM == 1) {
-        if (first) {
-          asm volatile("" ::: "memory");
-          if (lane == 0) atomicAdd(&L.issued, 1);
-          first = false;
-        }
-      }
-    };
-    for (int pos = lo + wv; pos < hi;) {
-      const uint32_t e = L.dent[pos];
-      const uint32_t row = e & 0x7fffffffu;
-      float g[BM], u[BM];
-      bool up;
-      // with 4 or 8 tokens the per-lane unit addresses of the row loads and
-      // token reads are formed again in every iteration (a few integer
-      // operations) rather than kept live across the loop, where they were
-      // spilled to scratch memory and read back in every iteration
-      int ln = lane;
-      if constexpr (BM >= 4) asm volatile("" : "+v"(ln));
-      // a row's requests and their use sit in one branch (row-uniform)
-      if constexpr (kI8) {
-        // INT8 rows: U8 = d / 16 units of 16 values; scales read as the row's
-        // requests go out, applied to the dot products
-        constexpr int NU8 = (NU + 1) / 2;
-        const int U8 = d >> 4;
-        const uint32_t urow = uniform(row);
-        if (gated && ((spec_ok && (e >> 31)) || no_as)) {
-          u32x4 vg[NU8], vu[NU8];
-          load_row<NU8>(a.wg + (size_t)urow * U8, U8, ln, vg);
-          load_row<NU8>(a.wu + (size_t)urow * U8, U8, ln, vu);
-          announce();
-          const float sgv = a.sg[urow], suv = a.su[urow];
-          row_dots_i8<BM, NU, true>(vg, vu, L.xs, U8, ln, g, u);
+    if constexpr (kMfmaUp) {
+      // INT8 weights, 3-8 tokens, on the matrix cores: a wave takes 4 rows at a
+      // time and multiplies them with 4 tokens per 4x4x4 MFMA, whose 16
+      // blocks take 16 pieces of the rows.  A request reads 256 bytes of each of
+      // the 4 rows (lane 4 p + n: the 16-byte piece p of row n), which is the
+      // MFMA's layout as it comes; the tokens come from LDS in the same
+      // layout, once for W_gate and W_up.  On the vector ALU (a row pair per
+      // wave, converted and multiplied with every token in turn) the phase
+      // was issue bound: the 8-token 7B call took 46.4 us, with this 35.9 (gate/up
+      // done at 23.8 us, now 15-18, of which the 45 MB of rows take 8).  fp16
+      // rows stay on the vector ALU: their phase is bound by the rows'
+      // bytes, and whole rows requested 1 KB at a time stream better than the
+      // 4 x 256 bytes here (4 tokens 24.2 us, this way 26.4; 8 tokens 41.7 and
+      // 41.1; with the rows turned around in registers instead 26.5 and 42.2).
+      typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+      typedef float f4 __attribute__((ext_vector_type(4)));
+      typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+      constexpr int TG = BM / 4;                     // token groups
+      constexpr int kWinMax = 2 * NU;                // 256-byte windows of a row, at most
+      const int rowu = d >> 4;                       // 16-byte units of a row
+      const int nwin = (rowu + 15) >> 4;
+      const int qp = lane >> 2, qn = lane & 3;
+      const u32x4* xa = &L.xs[qn * OwnedLds<BM, NU>::kStride + 2 * qp];
+      constexpr int kTG = 4 * OwnedLds<BM, NU>::kStride;  // from a token to the next group's
+      struct Acc {
+        f4 v[TG][2];  // token 4 tg + i of the lane's row, over the lane's pieces (two halves each)
+      };
+      auto mfma = [](u32x4 w, u32x4 x, f4(&c)[2]) {
+        c[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.x, x.y}),
+                                                  __builtin_bit_cast(h4, u2{w.x, w.y}), c[0], 0, 0, 0);
+        c[1] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.z, x.w}),
+                                                  __builtin_bit_cast(h4, u2{w.z, w.w}), c[1], 0, 0, 0);
+      };
+      // the tokens of window w in the MFMA's layout: the two 8-value halves of
+      // the lane's piece
+      struct Tok {
+        u32x4 v[TG][2];
+      };
+      auto tokens = [&](int w) -> Tok {
+        Tok x;
 #pragma unroll
-          for (int t = 0; t < BM; ++t) {
-            g[t] *= sgv;
-            u[t] *= suv;
+        for (int t = 0; t < TG; ++t) {
+          x.v[t][0] = xa[t * kTG + 32 * w];
+          x.v[t][1] = xa[t * kTG + 32 * w + 1];
+        }
+        return x;
+      };
+      // the products of a window of one or two matrices
+      auto window = [&](const Tok& x, u32x4 vg, u32x4 vu, Acc& ag, Acc& au, auto two) {
+        constexpr bool kTwo = decltype(two)::value;
+        u32x4 gl, gh, ul, uh;
+        i8_to_h16(vg, gl, gh);
+        if constexpr (kTwo) i8_to_h16(vu, ul, uh);
+#pragma unroll
+        for (int t = 0; t < TG; ++t) {
+          mfma(gl, x.v[t][0], ag.v[t]);
+          mfma(gh, x.v[t][1], ag.v[t]);
+          if constexpr (kTwo) {
+            mfma(ul, x.v[t][0], au.v[t]);
+            mfma(uh, x.v[t][1], au.v[t]);
           }
+        }
+      };
+      // the whole rows, kDepth windows of them in flight: a window's registers
+      // take the request kDepth windows on as soon as it is multiplied (the
+      // scheduling barriers keep the request there, and the tokens one window
+      // ahead).  Windows past the row's end request its last unit again and
+      // are left out of the products; in the last window of a row of an odd
+      // number of 128-byte lines the tokens' units past d are zero.
+      constexpr int kDepth = kWinMax < 8 ? kWinMax : 8;
+      auto rows = [&](const u32x4* pg, const u32x4* pu, Acc& ag, Acc& au, auto two) {
+        constexpr bool kTwo = decltype(two)::value;
+        u32x4 vg[kDepth], vu[kTwo ? kDepth : 1];
+        auto request = [&](int i, int w) {
+          const int u = min(16 * w + qp, rowu - 1);
+          vg[i] = load_nt(pg + u);
+          if constexpr (kTwo) vu[i] = load_nt(pu + u);
+        };
+#pragma unroll
+        for (int i = 0; i < kDepth; ++i) request(i, i);
+        SI_TRACE_WAVE(0);
+        int w0 = 0;
+        Tok x = tokens(0);
+#pragma unroll 1
+        for (; w0 + kDepth < nwin; w0 += kDepth) {
+#pragma unroll
+          for (int i = 0; i < kDepth; ++i) {
+            const Tok xn = tokens(w0 + i + 1);
+            window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
+            request(i, w0 + kDepth + i);
+            __builtin_amdgcn_sched_barrier(0);
+            x = xn;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kDepth; ++i) {
+          const Tok xn = tokens(min(w0 + i + 1, nwin - 1));
+          if (w0 + i < nwin) window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
+          x = xn;
+        }
+      };
+      // the lane's row's dot products, summed over the 16 pieces (every lane
+      // of the row has them)
+      auto total = [&](const Acc& acc, float(&o)[BM]) {
+#pragma unroll
+        for (int t = 0; t < BM; ++t) {
+          float v = acc.v[t >> 2][0][t & 3] + acc.v[t >> 2][1][t & 3];
+          v = dpp_add<0x124>(v);  // row_ror:4
+          v = dpp_add<0x128>(v);  // row_ror:8
+          v += __shfl_xor(v, 16, kWave);
+          o[t] = v + __shfl_xor(v, 32, kWave);
+        }
+      };
+      for (int pos = lo + kUpRows * uniform(wv); pos < hi;) {
+        const int cnt = min(kUpRows, hi - pos);
+        const uint32_t e = L.dent[pos + min(qn, cnt - 1)];  // the lane's row (a repeat of the last one past the end)
+        // rows whose W_up is requested with W_gate; the other lanes repeat one
+        // of them (no bytes of their own)
+        const bool early = gated && ((spec_ok && (e >> 31)) || no_as);
+        const uint32_t em = (uint32_t)__ballot(early && qn < cnt) & 0xfu;
+        auto row_of = [&](const u32x4* m, uint32_t mask) {
+          const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)e, __builtin_ctz(mask));
+          return m + (size_t)(((mask >> qn) & 1u ? e : f) & 0x7fffffffu) * rowu;
+        };
+        const float sgv = a.sg[e & 0x7fffffffu];
+        const float suv = gated ? a.su[e & 0x7fffffffu] : 1.f;
+        Acc ag = {}, au = {};
+        const u32x4* pg = a.wg + (size_t)(e & 0x7fffffffu) * rowu;
+        if (em)
+          rows(pg, row_of(a.wu, em), ag, au, std::true_type{});
+        else
+          rows(pg, pg, ag, au, std::false_type{});
+        float g[BM], u[BM];
+        total(ag, g);
+        total(au, u);
+        bool any = false;
+#pragma unroll
+        for (int t = 0; t < BM; ++t) {
+          g[t] = fmaxf(g[t] * sgv, 0.f);
+          any |= g[t] > 0.f;
+        }
+        // rows whose gate value asks for W_up only now (actual sparsity)
+        const uint32_t lm = (uint32_t)__ballot(any && gated && !early && qn < cnt) & 0xfu;
+        if (lm) {
+          Acc al = {}, unused;
+          rows(row_of(a.wu, lm), pg, al, unused, std::false_type{});
+          float v[BM];
+          total(al, v);
+#pragma unroll
+          for (int t = 0; t < BM; ++t) u[t] = (lm >> qn) & 1u ? v[t] : u[t];
+        }
+        const bool have_u = ((em | lm) >> qn) & 1u;
+        float hv = 0.f;  // lane 4 t + n: token t of row n
+#pragma unroll
+        for (int t = 0; t < BM; ++t)
+          hv = qp == t ? g[t] * (!gated ? 1.f : have_u ? u[t] * suv : 0.f) : hv;
+        if (qn < cnt && qp < b)
+          st_agent64(&a.h3e[(size_t)(e & 0x7fffffffu) * b + qp], tagged(tag, __float_as_uint(hv)));
+        n_up += __popc(em) + __popc(lm);
+        int nxt = hi;
+        if (lo + kUpRows * kOW < hi) {
+          if (lane == 0) nxt = atomicAdd(&L.gpos, kUpRows);
+          nxt = __builtin_amdgcn_readfirstlane(nxt);
+        }
+        pos = nxt;
+      }
+    } else {
+      // one token: a wave announces (LDS counter) that its first row's
+      // requests are out, so that the waves without a row can queue their
+      // W_down^T pieces behind them
+      bool first = BM == 1;
+      auto announce = [&]() {
+        if constexpr (BM == 1) {
+          if (first) {
+            asm volatile("" ::: "memory");
+            if (lane == 0) atomicAdd(&L.issued, 1);
+            first = false;
+          }
+        }
+      };
+      for (int pos = lo + wv; pos < hi;) {
+        const uint32_t e = L.dent[pos];
+        const uint32_t row = e & 0x7fffffffu;
+        float g[BM], u[BM];
+        bool up;
+        // with 4 or 8 tokens the per-lane unit addresses of the row loads and
+        // token reads are formed again in every iteration (a few integer
+        // operations) rather than kept live across the loop, where they were
+        // spilled to scratch memory and read back in every iteration
+        int ln = lane;
+        if constexpr (BM >= 4) asm volatile("" : "+v"(ln));
+        // a row's requests and their use sit in one branch (row-uniform)
+        if constexpr (kI8) {
+          // INT8 rows: U8 = d / 16 units of 16 values; scales read as the row's
+          // requests go out, applied to the dot products
+          constexpr int NU8 = (NU + 1) / 2;
+          const int U8 = d >> 4;
+          const uint32_t urow = uniform(row);
+          if (gated && ((spec_ok && (e >> 31)) || no_as)) {
+            u32x4 vg[NU8], vu[NU8];
+            load_row<NU8>(a.wg + (size_t)urow * U8, U8, lane, vg);
+            load_row<NU8>(a.wu + (size_t)urow * U8, U8, lane, vu);
+            announce();
+            const float sgv = a.sg[urow], suv = a.su[urow];
+            row_dots_i8<BM, NU, true>(vg, vu, L.xs, U8, lane, g, u);
+#pragma unroll
+            for (int t = 0; t < BM; ++t) {
+              g[t] *= sgv;
+              u[t] *= suv;
+            }
+            up = true;
+          } else {
+            u32x4 vg[NU8];
+            load_row<NU8>(a.wg + (size_t)urow * U8, U8, lane, vg);
+            announce();
+            const float sgv = a.sg[urow];
+            row_dots_i8<BM, NU, false>(vg, vg, L.xs, U8, lane, g, u);
+            bool any = false;
+#pragma unroll
+            for (int t = 0; t < BM; ++t) {
+              g[t] *= sgv;
+              any |= g[t] > 0.f;
+            }
+            up = gated && any;
+            if (up) {
+              u32x4 vu[NU8];
+              load_row<NU8>(a.wu + (size_t)urow * U8, U8, lane, vu);
+              if constexpr (BM >= 2) asm volatile("" ::: "memory");
+              const float suv = a.su[urow];
+              float unused[BM];
+              row_dots_i8<BM, NU, false>(vu, vu, L.xs, U8, lane, u, unused);
+#pragma unroll
+              for (int t = 0; t < BM; ++t) u[t] *= suv;
+            } else {
+#pragma unroll
+              for (int t = 0; t < BM; ++t) u[t] = gated ? 0.f : 1.f;
+            }
+          }
+        } else if (gated && ((spec_ok && (e >> 31)) || no_as)) {
+          u32x4 vg[NU], vu[NU];
+          load_row<NU>(a.wg + (size_t)row * U, U, ln, vg);
+          load_row<NU>(a.wu + (size_t)row * U, U, ln, vu);
+          announce();
+          SI_TRACE_WAVE(0);
+          row_dots2<BM, NU, XP>(vg, vu, L.xs, U, ln, g, u);
           up = true;
         } else {
-          u32x4 vg[NU8];
-          load_row<NU8>(a.wg + (size_t)urow * U8, U8, ln, vg);
+          u32x4 vg[NU];
+          load_row<NU>(a.wg + (size_t)row * U, U, ln, vg);
           announce();
-          const float sgv = a.sg[urow];
-          row_dots_i8<BM, NU, false>(vg, vg, L.xs, U8, ln, g, u);
+          row_dots<BM, NU, XP>(vg, L.xs, U, ln, g);
           bool any = false;
 #pragma unroll
-          for (int t = 0; t < BM; ++t) {
-            g[t] *= sgv;
-            any |= g[t] > 0.f;
-          }
+          for (int t = 0; t < BM; ++t) any |= g[t] > 0.f;
           up = gated && any;
           if (up) {
-            u32x4 vu[NU8];
-            load_row<NU8>(a.wu + (size_t)urow * U8, U8, ln, vu);
+            u32x4 vu[NU];
+            load_row<NU>(a.wu + (size_t)row * U, U, ln, vu);
+            // the tokens are read from LDS again: kept from the gate products,
+            // 2..8 tokens' units would not fit in registers and were spilled
             if constexpr (BM >= 2) asm volatile("" ::: "memory");
-            const float suv = a.su[urow];
-            float unused[BM];
-            row_dots_i8<BM, NU, false>(vu, vu, L.xs, U8, ln, u, unused);
-#pragma unroll
-            for (int t = 0; t < BM; ++t) u[t] *= suv;
-          } else {
+            row_dots<BM, NU, XP>(vu, L.xs, U, ln, u);
+          } else {  // h3 = ReLU(g) * 1 without W_up
 #pragma unroll
             for (int t = 0; t < BM; ++t) u[t] = gated ? 0.f : 1.f;
           }
         }
-      } else if (gated && ((spec_ok && (e >> 31)) || no_as)) {
-        u32x4 vg[NU], vu[NU];
-        load_row<NU>(a.wg + (size_t)row * U, U, ln, vg);
-        load_row<NU>(a.wu + (size_t)row * U, U, ln, vu);
-        announce();
-        SI_TRACE_WAVE(0);
-        row_dots2<BM, NU>(vg, vu, L.xs, U, ln, g, u);
-        up = true;
-      } else {
-        u32x4 vg[NU];
-        load_row<NU>(a.wg + (size_t)row * U, U, ln, vg);
-        announce();
-        row_dots<BM, NU>(vg, L.xs, U, ln, g);
-        bool any = false;
+        n_up += up ? 1 : 0;
+        float hv = 0.f;  // lane t holds token t's h3
 #pragma unroll
-        for (int t = 0; t < BM; ++t) any |= g[t] > 0.f;
-        up = gated && any;
-        if (up) {
-          u32x4 vu[NU];
-          load_row<NU>(a.wu + (size_t)row * U, U, ln, vu);
-          // the tokens are read from LDS again: kept from the gate products,
-          // 2..8 tokens' units would not fit in registers and were spilled
-          if constexpr (BM >= 2) asm volatile("" ::: "memory");
-          row_dots<BM, NU>(vu, L.xs, U, ln, u);
-        } else {  // h3 = ReLU(g) * 1 without W_up
-#pragma unroll
-          for (int t = 0; t < BM; ++t) u[t] = gated ? 0.f : 1.f;
+        for (int t = 0; t < BM; ++t) hv = lane == t ? fmaxf(g[t], 0.f) * u[t] : hv;
+        if (lane < b) st_agent64(&a.h3e[(size_t)row * b + lane], tagged(tag, __float_as_uint(hv)));
+        // the next free position of the member's range: the waves that the
+        // CU serves first take more rows (with a fixed stride the second wave
+        // of each SIMD finished its rows up to 10 us after the first); with at
+        // most one position per wave there is none, and no wave waits for
+        // the counter
+        int nxt = hi;
+        if (lo + kOW < hi) {
+          if (lane == 0) nxt = atomicAdd(&L.gpos, 1);
+          nxt = __builtin_amdgcn_readfirstlane(nxt);
         }
+        pos = nxt;
       }
-      n_up += up ? 1 : 0;
-      float hv = 0.f;  // lane t holds token t's h3
-#pragma unroll
-      for (int t = 0; t < BM; ++t) hv = lane == t ? fmaxf(g[t], 0.f) * u[t] : hv;
-      if (lane < b) st_agent64(&a.h3e[(size_t)row * b + lane], tagged(tag, __float_as_uint(hv)));
-      // the next free position of the member's range: the waves that the
-      // CU serves first take more rows (with a fixed stride the second wave
-      // of each SIMD finished its rows up to 10 us after the first); with at
-      // most one position per wave there is none, and no wave waits for
-      // the counter
-      int nxt = hi;
-      if (lo + kOW < hi) {
-        if (lane == 0) nxt = atomicAdd(&L.gpos, 1);
-        nxt = __builtin_amdgcn_readfirstlane(nxt);
-      }
-      pos = nxt;
     }
     SI_TRACE_WAVE(1);
     if constexpr (BM == 1 && kI8) {
@@ -1085,7 +1259,6 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // row's pieces are requested (with several tokens a kept row almost
     // always has a non-zero h3; without speculation the rounds below run)
     bool pipelined = false;
-    constexpr bool kMfma = BM >= 4;
     bool mdone = false;      // the down item ran on the matrix cores (its tile is in macc)
     float macc[4][4] = {};   // column block cb of the wave, D[4 g + i][token]: column 64 wv + 16 cb + 4 g + i
     if constexpr (kMfma) {

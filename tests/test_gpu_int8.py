@@ -219,6 +219,28 @@ def test_int8_edge_shapes(k, d, b):
             check(c, m_ref, y, cnt)
 
 
+@pytest.mark.parametrize("k,d,b,gated", [(5, 128, 8, True), (300, 256, 4, True), (1030, 384, 3, False),
+                                         (901, 2176, 5, True), (1200, 4096, 8, False), (2050, 4224, 6, True),
+                                         (515, 8192, 4, True)])
+def test_int8_tokens_4x4_windows(k, d, b, gated):
+    """3-8 tokens: rows taken four at a time in windows of 256 values, eight
+    of them in flight (d = 128 and 384: the last window half full; 2176: one
+    past the eight; 4224: a window past two eights; shares of 1-5 rows, so
+    that fours are partly empty).  Without speculation W_up waits for the
+    gate values of each four, with SI_NO_AS all rows are read."""
+    rng = np.random.default_rng(31 * k + d + b)
+    c = I8Case(rand_bits(rng, (k, d)), rand_bits(rng, (k, d)) if gated else None, rand_bits(rng, (d, k)),
+               rand_bits(rng, (b, d)), max_batch=b)
+    for alpha, flags in [(math.inf, 0), (1.0, si.SI_NO_SPECULATION), (1.03, si.SI_NO_AS | si.SI_NO_SPECULATION)]:
+        print(f"k={k} d={d} b={b} gated={gated} alpha={alpha} flags={flags}", flush=True)
+        fused(c, alpha, flags)
+    m = rng.random(k) < 0.4
+    m[k // 2] = True
+    y, cnt = c.layer.sparse_mlp(to_dev(c.x), torch.from_numpy(m.astype(np.uint8)).to(DEV), counters=True)
+    torch.cuda.synchronize()
+    check(c, m, y, cnt)
+
+
 @pytest.mark.parametrize("k,d,gated", [(9000, 8192, True), (40000, 2048, True), (20000, 4096, False)])
 def test_int8_one_token_large_groups(k, d, gated):
     """One token with groups of more than 512 rows (T = ceil(d / 512) blocks
