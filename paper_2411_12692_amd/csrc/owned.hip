@@ -423,9 +423,9 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   // them) the call counter; addresses are clamped so that the requests are
   // unconditional and go out back to back; tokens b..BM-1 are zero
   // a row has d/128 <= 4 NU sign units, so a wave counts at most
-  // ceil(NU / 2) of them per pass; the requests are unconditional (clamped
-  // unit, the same line again where a wave has fewer) so that the counts
-  // can start as the first ones arrive
+  // ceil(NU / 2) consecutive ones of them per pass; the requests are
+  // unconditional (clamped unit, the same line again where a wave has fewer)
+  // so that the counts can start as the first ones arrive
   constexpr int kSU = (NU + 1) / 2;
   static_assert(kSU <= kOSignUnits, "sign units per wave");
   u32x4 sreg[kSU];
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     const u32x4* sg = a.signs + r0 + min(s * kWave + lane, Rb - 1);
 #pragma unroll
     for (int i = 0; i < kSU; ++i) {
-      const int q = min(wv + kOW * i, units - 1);
+      const int q = min(wv * kSU + i, units - 1);
       sreg[i] = load_nt(sg + (size_t)q * kpad);
     }
   };
@@ -579,32 +579,33 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       }
     }
   };
-  if constexpr (!block_mode && BM == 1) {
-    const u32x4* xg = reinterpret_cast<const u32x4*>(a.x);
-    for (int i = tid; i < XS; i += kOT) {
-      const u32x4 xv = xg[min(i, U - 1)];
-      if (i == tid && tid == 0) {
-        asm volatile("" ::: "memory");
-        load_epoch(a.hdr, L.epoch, L.err);
-        L.n_up = 0;
-        L.n_down = 0;
-      }
-      L.xs[i] = i < U ? xv : u32x4{0, 0, 0, 0};
+  // partial N_neg counts of the wave's sign units for the rows of the pass
+  // (lane = row), summed by the finishing wave
+  int c[BM];
+  auto count_token = [&](int t) {
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < kSU; ++i) {
+      const int q = wv * kSU + i;
+      const int qc = min(q, units - 1);
+      const u32x4 xv = *reinterpret_cast<const u32x4*>(&L.xw[t * W + 4 * qc]);
+      const int nq = __popc(sreg[i].x ^ xv.x) + __popc(sreg[i].y ^ xv.y) + __popc(sreg[i].z ^ xv.z) +
+                     __popc(sreg[i].w ^ xv.w);
+      n += q < units ? nq : 0;
     }
-  } else if constexpr (!block_mode) {
-    // with 2-8 tokens every unit of the thread is requested before any is
-    // stored, so that the requests travel together (a load-store loop
-    // waits once per unit: 2 us of 64 KB with 8 tokens)
+    c[t] = n;
+  };
+  if constexpr (!block_mode) {
     const u32x4* xg = reinterpret_cast<const u32x4*>(a.x);
     const int nx = b * U;
-    constexpr int JX = (BM * XS + kOT - 1) / kOT;
-    if constexpr (BM == 4) {
-      // 3-4 tokens: the units go straight from memory into LDS
+    if (BM == 4 && !predict) {
+      // 3-4 tokens and a mask: the units go straight from memory into LDS
       // (global_load_lds, 16 bytes per lane, a wave's 64 consecutive units of
       // xs) without passing through registers; units past a token's d or of
       // tokens b..BM-1 are zeroed once the copies have landed.  (The 4-token
       // mask call 24.37 -> 23.76 us; with 2 and 8 tokens the same copies were
       // 0.1-0.3 us slower than the loads below.)
+      constexpr int JX = (BM * XS + kOT - 1) / kOT;
       static_assert(XS % kWave == 0, "a wave's units of xs lie within one token");
 #pragma unroll
       for (int j = 0; j < JX; ++j) {
@@ -628,11 +629,19 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         if (i < BM * XS && !(t < b && u < U)) L.xs[t * XP + u] = u32x4{0, 0, 0, 0};
       }
     } else {
-      u32x4 xv[JX];
+      // the wave stages the tokens' 16-byte units that its own sign units
+      // cover (kXW of each token), so that it forms their sign bytes and
+      // counts with no block barrier in between (sign words formed from the
+      // staged tokens between two barriers: one token, 7B 12.33 us, so 12.00;
+      // INT8 11.45 and 11.15).  Every unit is requested before any is stored, so that the
+      // requests travel together (a load-store loop waits once per unit: 2
+      // us of 64 KB with 8 tokens).
+      constexpr int kXW = 16 * kSU, JW = (BM * kXW + kWave - 1) / kWave;
+      u32x4 xv[JW];
 #pragma unroll
-      for (int j = 0; j < JX; ++j) {
-        const int i = tid + j * kOT, t = i / XS, u = i - t * XS;
-        xv[j] = xg[min(t * U + u, nx - 1)];
+      for (int j = 0; j < JW; ++j) {
+        const int i = lane + j * kWave, t = i / kXW, u = wv * kXW + i - t * kXW;
+        xv[j] = xg[min(min(t, b - 1) * U + min(u, U - 1), nx - 1)];
       }
       if (tid == 0) {
         asm volatile("" ::: "memory");
@@ -641,9 +650,20 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         L.n_down = 0;
       }
 #pragma unroll
-      for (int j = 0; j < JX; ++j) {
-        const int i = tid + j * kOT, t = i / XS, u = i - t * XS;
-        if (i < BM * XS) L.xs[t * XP + u] = (t < b && u < U) ? xv[j] : u32x4{0, 0, 0, 0};
+      for (int j = 0; j < JW; ++j) {
+        const int i = lane + j * kWave, t = i / kXW, u = wv * kXW + i - t * kXW;
+        if (t < BM && u < XS) {
+          const u32x4 v = (t < b && u < U) ? xv[j] : u32x4{0, 0, 0, 0};
+          L.xs[t * XP + u] = v;
+          if (predict && u < U) reinterpret_cast<uint8_t*>(L.xw)[t * 4 * W + u] = (uint8_t)sign_byte(v);
+        }
+        // (one token: here; in a pass after the loop the 7B call took 12.23
+        // instead of 12.01 us)
+        if (BM == 1 && j == JW - 1 && predict && Rb > 0) count_token(0);
+      }
+      if (BM > 1 && predict && Rb > 0) {
+#pragma unroll
+        for (int t = 0; t < BM; ++t) count_token(t);
       }
     }
   } else {
@@ -727,6 +747,23 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       if (lane == 0) L.nsum[wv][t] = v;
     }
   }
+  if constexpr (block_mode) {  // (the sign bytes are other waves' there; with
+    // the units of h dealt like the sign units, and so without this barrier, the
+    // one-token call took 13.1 instead of 12.85 us)
+    __syncthreads();
+    if constexpr (!kKeep) scale_units();  // before the counts, not behind the publishing stores
+    if (Rb > 0) {
+#pragma unroll
+      for (int t = 0; t < BM; ++t) count_token(t);
+    }
+  }
+  // every wave stores its partial counts of the first 64 rows (zero without
+  // units); the barrier also covers the staged tokens and the call counter
+  auto store_counts = [&]() {
+#pragma unroll
+    for (int t = 0; t < BM; ++t) L.cpart[wv][t][lane] = c[t];
+  };
+  if (predict && Rb > 0) store_counts();
   __syncthreads();
   // a workspace left inconsistent by a call whose bounded wait gave up (its
   // sticky error word is set): nothing is computed until the workspace is
@@ -735,22 +772,12 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     if (owns_tile && wv == kTileWave) poison_tile(a.y, b, d, blk, lane);
     return;
   }
-  if constexpr (block_mode && !kKeep) scale_units();  // before the counts, not behind the publishing stores
   const uint32_t epoch = uniform(L.epoch);
   const uint32_t tag = epoch_tag(epoch);
   // consumed here, where the wait for it is covered by the token requests (a
   // load left outstanding into the loop below would make the compiler wait
   // for every outstanding request, stores included, inside it)
   bool mkeep = mbyte != 0;
-  if constexpr (!block_mode) {  // (written with the norm, before the barrier above, in decoder-block mode)
-    if (predict) {
-      for (int i = tid; i < BM * W; i += kOT) {  // tokens b..BM-1 are zero
-        const int t = i / W, w = i - t * W;
-        L.xw[i] = sign_word(&L.xs[t * XP + 4 * w]);
-      }
-    }
-    __syncthreads();
-  }
   SI_TRACE_MARK(1);
 
   // ---- 1. kept and confident masks of the owned rows, 64 rows per pass;
@@ -759,28 +786,12 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   int n_own = 0;  // finishing wave
   for (int s = 0; s < nsub; ++s) {
     const bool any_rows = s * kWave < Rb;
-    if (predict && any_rows) {
-      if (s > 0) load_signs(s);
-      int c[BM];
+    if (s > 0 && predict && any_rows) {
+      load_signs(s);
 #pragma unroll
-      for (int t = 0; t < BM; ++t) c[t] = 0;
-#pragma unroll
-      for (int i = 0; i < kSU; ++i) {
-        const int q = wv + kOW * i;
-        const int qc = min(q, units - 1);
-#pragma unroll
-        for (int t = 0; t < BM; ++t) {
-          const u32x4 xv = *reinterpret_cast<const u32x4*>(&L.xw[t * W + 4 * qc]);
-          const int n = __popc(sreg[i].x ^ xv.x) + __popc(sreg[i].y ^ xv.y) + __popc(sreg[i].z ^ xv.z) +
-                        __popc(sreg[i].w ^ xv.w);
-          c[t] += q < units ? n : 0;
-        }
-      }
-      // every wave stores its partial counts (zero without units)
-#pragma unroll
-      for (int t = 0; t < BM; ++t) L.cpart[wv][t][lane] = c[t];
+      for (int t = 0; t < BM; ++t) count_token(t);
+      store_counts();
       __syncthreads();
-      if (s == 0) SI_TRACE_MARK(2);
     }
     if (wv == kFin) {
       // every request of this wave has completed here (the sign units for
