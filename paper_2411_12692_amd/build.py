@@ -21,7 +21,7 @@ BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libsparseinfer.so")
 TRACE_LIB = os.path.join(PKG, "libsparseinfer_trace.so")
 TRACED = "owned.hip"  # the source compiled with -DSI_TRACE in the trace variant
-SOURCES = ["api.hip", "pack.hip", "predict.hip", "mlp.hip", "layer.hip", "owned.hip", "diag.hip"]
+SOURCES = ["api.hip", "pack.hip", "predict.hip", "mlp.hip", "owned.hip", "diag.hip"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc" if os.path.exists("/opt/rocm/bin/hipcc") else "hipcc")

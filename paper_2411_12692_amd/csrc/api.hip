@@ -156,7 +156,7 @@ si_status si_read_bandwidth_probe(const void* buf, size_t bytes, uint32_t* sink,
 
 int si_single_launch(int k, int d, int b) {
   if (check_kd(k, d) != SI_OK || check_b(b) != SI_OK) return 0;
-  return si::layer_supported(k, d, b) && si::owned_supported(k, d, b) ? 1 : 0;
+  return si::owned_supported(k, d, b) ? 1 : 0;
 }
 
 int32_t si_alpha_threshold(float alpha, int d) {
@@ -264,18 +264,7 @@ si_status sparse_mlp_impl(const uint16_t* w_gate, const uint16_t* w_up, const ui
   hipStream_t st = (hipStream_t)stream;
   const si::WsLayout L = si::ws_layout(k, b);
   char* base = static_cast<char*>(workspace);
-  if (active_idx && b > 4 && si::owned_supported(k, d, b)) {
-    // With 5-8 tokens the list-driven kernel (16 waves per block, so at most
-    // 128 registers per lane) spills; the list becomes a mask in the
-    // workspace and the row-owning kernel (8 waves) runs in mask mode.
-    uint8_t* wmask = reinterpret_cast<uint8_t*>(base + L.mask);
-    if (si_status s = hip_status(si::launch_list_to_mask(active_idx, n_active, k, wmask, st), "list launch"))
-      return s;
-    mask = wmask;
-    active_idx = nullptr;
-    n_active = nullptr;
-  }
-  if (active_idx ? si::layer_supported(k, d, b) : si::owned_supported(k, d, b)) {
+  if (active_idx ? si::list_supported(k, d, b) : si::owned_supported(k, d, b)) {
     si::LayerCall c;
     c.w_gate = w_gate;
     c.w_up = w_up;
@@ -291,10 +280,10 @@ si_status sparse_mlp_impl(const uint16_t* w_gate, const uint16_t* w_up, const ui
     if (active_idx) {
       c.idx_in = active_idx;
       c.n_in = n_active;
-      return hip_status(si::launch_layer(c, st), "sparse_mlp launch");
+    } else {
+      c.mask_in = mask;
+      c.n_out = reinterpret_cast<int32_t*>(base) + si::H_N_INTERNAL;  // n_gate of the counters
     }
-    c.mask_in = mask;
-    c.n_out = reinterpret_cast<int32_t*>(base) + si::H_N_INTERNAL;  // n_gate of the counters
     return hip_status(si::launch_owned(c, st), "sparse_mlp launch");
   }
   if (!active_idx) {

@@ -10,53 +10,30 @@
 
 namespace si {
 
-// One block walks the rows in chunks of 1024 with a running count of the
-// kept rows (the list position of a kept row when the call took a list).
 // Kept rows get the value the call published for them in this call, or NaN
 // when there is none; other rows get 0.
 __global__ __launch_bounds__(1024) void k_read_h3(const uint32_t* __restrict__ hdr, const uint64_t* __restrict__ h3e,
                                                   const float* __restrict__ h3p, const uint8_t* __restrict__ mask,
                                                   int k, int b, float* __restrict__ out) {
-  __shared__ int wsum[16];
-  __shared__ int base;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const uint32_t form = hdr[H_H3_FORM];
   const uint32_t tag = epoch_tag(hdr[H_EPOCH] - 1u);  // the last call's tag (each call advances the counter once)
   const float nan = __builtin_nanf("");
-  if (tid == 0) base = 0;
-  __syncthreads();
-  for (int off = 0; off < k; off += 1024) {
-    const int i = off + tid;
-    const bool kept = i < k && mask[i] != 0;
-    const uint64_t bal = __ballot(kept);
-    if (lane == 0) wsum[wv] = __popcll(bal);
-    __syncthreads();
-    int pos = base;
-    for (int w = 0; w < wv; ++w) pos += wsum[w];
-    pos += __popcll(bal & lanes_below(lane));
-    if (i < k) {
-      for (int t = 0; t < b; ++t) {
-        float v = 0.f;
-        if (kept) {
-          if (form == kH3ByRow || form == kH3ByPos) {
-            const uint64_t w = h3e[(size_t)(form == kH3ByRow ? i : pos) * b + t];
-            v = (uint32_t)(w >> 32) == tag ? __uint_as_float((uint32_t)w) : nan;
-          } else if (form == kH3PlainByRow) {
-            v = h3p[(size_t)i * b + t];
-          } else {
-            v = nan;
-          }
+  for (int i = threadIdx.x; i < k; i += 1024) {
+    const bool kept = mask[i] != 0;
+    for (int t = 0; t < b; ++t) {
+      float v = 0.f;
+      if (kept) {
+        if (form == kH3ByRow) {
+          const uint64_t w = h3e[(size_t)i * b + t];
+          v = (uint32_t)(w >> 32) == tag ? __uint_as_float((uint32_t)w) : nan;
+        } else if (form == kH3PlainByRow) {
+          v = h3p[(size_t)i * b + t];
+        } else {
+          v = nan;
         }
-        out[(size_t)i * b + t] = v;
       }
+      out[(size_t)i * b + t] = v;
     }
-    __syncthreads();
-    if (tid == 0) {
-      int s = 0;
-      for (int w = 0; w < 16; ++w) s += wsum[w];
-      base += s;
-    }
-    __syncthreads();
   }
 }
 

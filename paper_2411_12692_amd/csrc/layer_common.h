@@ -1,8 +1,7 @@
-// Pieces shared by the single-launch layer kernels (layer.hip: list-driven
-// and predictor-only calls; owned.hip: row-owning predict/mask calls):
-// constants, wave-level reductions and scans, tagged exchange words, the
-// row loads and dot products of the gate/up phase, and the host-side
-// template dispatch.
+// Pieces of the single-launch kernel (owned.hip), some shared with the
+// multi-launch path: constants, wave-level reductions and scans, tagged
+// exchange words, the row loads and dot products of the gate/up phase, and the
+// host-side template dispatch.
 #pragma once
 
 #include "si_device.h"
@@ -10,14 +9,6 @@
 
 namespace si {
 
-constexpr int kLWaves = 16;
-constexpr int kLThreads = kLWaves * kWave;
-constexpr int kMaxSignUnitsPerWave = (kMaxD / 128 + kLWaves - 1) / kLWaves;  // 4
-constexpr int kRoundRows = kLWaves / 2;    // gate/up rows per round: one (row, matrix) item per wave
-constexpr int kDN = 4;                     // down pieces in flight per wave
-constexpr int kDownRound = kLWaves * kDN;  // down positions per round
-constexpr int kMaxDownItem = 4096;         // positions of one down item (at most)
-constexpr int kDownPollThreads = 256;      // waves 0..3 collect a round's h3 words
 constexpr int kMinLds = 96 * 1024;         // more than half of a CU's LDS: one block per CU
 constexpr int kMaxLds = 160 * 1024;
 constexpr long kPollLimit = 1l << 16;
@@ -63,48 +54,6 @@ __device__ inline int wave_incl_scan(int v) {
   v += dpp_get<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
   v += dpp_get<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
   return v;
-}
-
-// Poll one tagged word per lane (lanes may use different addresses) until it
-// carries `tag`; returns the payload.  After the spin limit the wave stops
-// waiting (`abort`) and the error bit is set.
-__device__ inline uint32_t poll_lane(const uint64_t* p, bool active, uint32_t tag, uint32_t* hdr, bool& abort) {
-  uint32_t out = 0;
-  bool pending = active;
-  long spins = 0;
-  while (__ballot(pending) && !abort) {
-    if (pending) {
-      const uint64_t v = ld_agent64(p);
-      if ((uint32_t)(v >> 32) == tag) {
-        out = (uint32_t)v;
-        pending = false;
-      }
-    }
-    if (__ballot(pending)) {
-      if (++spins > kPollLimit) {
-        abort = true;
-        if (pending) atomicOr(&hdr[H_ERR], kErrLookbackSpin);
-      } else {
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
-  }
-  return out;
-}
-
-// Threads [0, nthreads) wait until every block's alive word carries `tag`.
-__device__ inline void wait_alive(const uint64_t* alive, int blocks, int t, int nthreads, uint32_t tag,
-                                  uint32_t* hdr) {
-  for (int j = t; j < blocks; j += nthreads) {
-    long spins = 0;
-    while ((uint32_t)(ld_agent64(&alive[j]) >> 32) != tag) {
-      if (++spins > kPollLimit) {
-        atomicOr(&hdr[H_ERR], kErrLookbackSpin);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(1);
-    }
-  }
 }
 
 // Block 0, once every block has read the call counter: advance it.

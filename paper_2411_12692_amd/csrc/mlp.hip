@@ -13,12 +13,10 @@
 // atomics (y was zeroed by the gate/up kernel).  With 8 tiles the tile is
 // blockIdx % 8, i.e. the XCD, so every atomic on a y tile stays on one XCD.
 // One extra block sums the per-block work counters when they are requested.
-#include "si_device.h"
-#include "si_launch.h"
+#include "layer_common.h"
 
 namespace si {
 
-constexpr uint32_t kNoAS = 1u;
 constexpr int kDownChunks = 32;
 constexpr int kDownWaves = 8;
 
@@ -154,6 +152,38 @@ __global__ __launch_bounds__(kDownWaves * kWave) void k_down(
     const float v = (&red[0][0])[i];
     if (col < d && v != 0.f) unsafeAtomicAdd(&y[(size_t)t * d + col], v);
   }
+}
+
+// Sum of the per-block work counts -> counters[3] = {n_gate, n_up, n_down}.
+__global__ __launch_bounds__(256) void k_sum_counts(const int32_t* __restrict__ counts, int slots,
+                                                    const int32_t* __restrict__ n_active, int k,
+                                                    int32_t* __restrict__ counters) {
+  __shared__ int s[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (tid < 2) s[tid] = 0;
+  __syncthreads();
+  int u = 0, dn = 0;
+  for (int i = tid; i < slots; i += 256) {
+    u += counts[2 * i];
+    dn += counts[2 * i + 1];
+  }
+  u = wave_sum_int(u);
+  dn = wave_sum_int(dn);
+  if (lane == 0) {
+    atomicAdd(&s[0], u);
+    atomicAdd(&s[1], dn);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    counters[0] = min(max(*n_active, 0), k);
+    counters[1] = s[0];
+    counters[2] = s[1];
+  }
+}
+hipError_t launch_sum_counts(const int32_t* counts, int slots, const int32_t* n_active, int k, int32_t* counters,
+                             hipStream_t s) {
+  k_sum_counts<<<1, 256, 0, s>>>(counts, slots, n_active, k, counters);
+  return hipGetLastError();
 }
 
 template <int B>

@@ -3,7 +3,7 @@
 // sparse gate/up with actual sparsity and the sparse down-projection
 // (Section IV-B 3)-4)), for decode batches of up to 8 tokens.
 //
-// One block of 16 wavefronts per compute unit, all blocks resident at once.
+// One block of 8 wavefronts per compute unit, all blocks resident at once.
 // With T = 512-column tiles of y, the blocks form groups of T consecutive
 // blocks; block b of the first (P / T) T owns rows [b R, (b + 1) R).
 //
@@ -38,6 +38,10 @@
 // signs (the MSBs of the INT8 weights), gate/up converts each row's INT8
 // values exactly to fp16 in registers and scales the dot products, and the
 // down-projection scales each column of y once, at the tile's add.
+//
+// A caller's list (the kernel's fourth form) needs no prediction and no mask
+// exchange: each group takes an even slice of the list as its kept rows, and
+// its members go on from there.
 //
 // No block waits for the whole grid: the only exchanges are inside a group.
 // One block (the last, where the grid has a block without rows, else block 0)
@@ -134,6 +138,8 @@ struct OwnedArgs {
   const float* sd;
   const uint16_t* x;
   const uint8_t* mask_in;  // mask mode (else predict mode)
+  const int32_t* idx_in;   // list form: the caller's kept rows and their count
+  const int32_t* n_in;
   int k, d, b, T, margin;
   uint32_t flags;
   int mlp;
@@ -386,6 +392,7 @@ struct DownPiece<true> {
 constexpr int kModePlain = 0;  // fp16 weights, x given
 constexpr int kModeBlock = 1;  // fp16 weights, x = RMSNorm(h) * norm_w, y = h + MLP
 constexpr int kModeInt8 = 2;   // INT8 weights with per-channel scales, x given
+constexpr int kModeList = 3;   // fp16 weights, x given, the rows from a caller's list
 
 // MODE: the kernel's form (above); each is a separate instance so that the
 // plain form carries none of the others' code (the decoder-block code alone
@@ -408,8 +415,9 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   // rows where the grid has one (the census waits for the last block to
   // publish, which a block with rows would wait for before its gate/up)
   const int cblk = a.groups * T < P ? P - 1 : 0;
-  const int Rb = blk < a.groups * T ? max(0, min(R, k - r0)) : 0;  // rows this block owns
-  const bool predict = a.mask_in == nullptr;
+  constexpr bool kList = MODE == kModeList;
+  const int Rb = !kList && blk < a.groups * T ? max(0, min(R, k - r0)) : 0;  // rows this block owns
+  const bool predict = !kList && a.mask_in == nullptr;
   const bool no_as = (a.flags & kNoAS) != 0;
   const bool spec_ok = (a.flags & kNoSpec) == 0;
   const bool gated = a.wu != nullptr;  // else the non-gated ReLU MLP (no W_up)
@@ -438,6 +446,17 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       sreg[i] = load_nt(sg + (size_t)q * kpad);
     }
   };
+  // list form: the group's rows are an even slice of the list, the same for
+  // each of its blocks (the first 512 entries are requested ahead of the tokens)
+  int lp0 = 0, lcnt = 0, lrow = 0;
+  if constexpr (kList) {
+    if (blk < a.groups * T) {
+      const long long nl = min(max(*a.n_in, 0), k);
+      lp0 = (int)(nl * (blk / T) / a.groups);
+      lcnt = (int)(nl * (blk / T + 1) / a.groups) - lp0;
+    }
+    if (tid < lcnt) lrow = a.idx_in[lp0 + tid];
+  }
   uint32_t mbyte = 0;
   if (Rb > 0) {
     if (predict) load_signs(0);
@@ -764,7 +783,30 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     for (int t = 0; t < BM; ++t) L.cpart[wv][t][lane] = c[t];
   };
   if (predict && Rb > 0) store_counts();
-  __syncthreads();
+  if constexpr (kList) {
+    bool bad = false;
+    for (int q = tid; q < lcnt; q += kOT) {
+      const int r = q == tid ? lrow : a.idx_in[lp0 + q];
+      const bool in = (unsigned)r < (unsigned)k;
+      L.dent[q] = in ? (uint32_t)r | 0x80000000u : kBadRow;  // given rows count as confident
+      bad |= !in;
+    }
+    if (bad) atomicOr(&a.hdr[H_ERR], kErrRow);
+    // entries outside [0, k) are left out (each block of the group does the
+    // same, so that its members agree on the positions)
+    if (__syncthreads_or(bad)) {
+      if (tid == 0) {
+        int n = 0;
+        for (int q = 0; q < lcnt; ++q)
+          if (L.dent[q] != kBadRow) L.dent[n++] = L.dent[q];
+        L.n_own = n;
+      }
+      __syncthreads();
+      lcnt = uniform(L.n_own);
+    }
+  } else {
+    __syncthreads();
+  }
   // a workspace left inconsistent by a call whose bounded wait gave up (its
   // sticky error word is set): nothing is computed until the workspace is
   // reset, and the owners of the tiles of y fill them with NaN
@@ -779,6 +821,9 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   // for every outstanding request, stores included, inside it)
   bool mkeep = mbyte != 0;
   SI_TRACE_MARK(1);
+  if constexpr (kList) {  // this block has read the call counter
+    if (tid == 0) st_agent64(&a.pub[(size_t)blk * kOwnPubStride + kCountWord], tagged(tag, 0u));
+  }
 
   // ---- 1. kept and confident masks of the owned rows, 64 rows per pass;
   // the finishing wave applies the rule, lists the kept rows in order and
@@ -885,19 +930,19 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // the census block's waves 4..7 meanwhile take the census: every block's
     // kept count (the call's count, and proof that every block has read the
     // call counter, which the census block then advances)
-    if (tid < 4 * npairs) {
+    if (!kList && tid < 4 * npairs) {
       const int p = tid >> 2;
       const int o = g * T + p / nsub, sb = p - (p / nsub) * nsub;
       const uint64_t* src[1] = {&a.pub[(size_t)o * kOwnPubStride + 4 * sb + (tid & 3)]};
       uint32_t v[1];
       poll_words<1>(src, 1, tag, a.hdr, v);
       L.pm[tid] = v[0];
-    } else if (blk == cblk && tid >= kOT / 2) {
+    } else if (!kList && blk == cblk && tid >= kOT / 2) {
       const int sum = wave_sum_int(census_part(a.pub, P, tid - kOT / 2, kOT / 2, tag, a.hdr));
       if (lane == 0) L.wsum[wv] = sum;
     }
-    __syncthreads();
-    if (blk == cblk && tid == 0) {
+    if constexpr (!kList) __syncthreads();
+    if (!kList && blk == cblk && tid == 0) {
       int sum = 0;
       for (int w = kOW / 2; w < kOW; ++w) sum += L.wsum[w];
       if (a.n_out) *a.n_out = sum;
@@ -920,19 +965,22 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // the group's kept rows in order: every wave forms the prefix of the
     // pairs' kept counts (lane = pair), then one wave per pair writes its
     // rows' entries (lane = row)
-    const int cnt = lane < npairs ? __popc(L.pm[4 * lane]) + __popc(L.pm[4 * lane + 1]) : 0;
-    const int incl = wave_incl_scan(cnt);
-    const int pre = incl - cnt;
-    const int n = min(uniform(__builtin_amdgcn_readlane(incl, kWave - 1)), kMaxChunkRows);
-    for (int p = wv; p < npairs; p += kOW) {
-      const uint64_t kb = (uint64_t)L.pm[4 * p] | ((uint64_t)L.pm[4 * p + 1] << 32);
-      const uint64_t cb = (uint64_t)L.pm[4 * p + 2] | ((uint64_t)L.pm[4 * p + 3] << 32);
-      const int q0p = __builtin_amdgcn_readlane(pre, p);
-      if ((kb >> lane) & 1ull) {
-        const int o = g * T + p / nsub, sb = p - (p / nsub) * nsub;
-        const uint32_t row = (uint32_t)(o * R + sb * kWave + lane);
-        const int q = q0p + __popcll(kb & lanes_below(lane));
-        if (q < kMaxChunkRows) L.dent[q] = row | (((cb >> lane) & 1ull) ? 0x80000000u : 0u);
+    int n = lcnt;
+    if constexpr (!kList) {
+      const int cnt = lane < npairs ? __popc(L.pm[4 * lane]) + __popc(L.pm[4 * lane + 1]) : 0;
+      const int incl = wave_incl_scan(cnt);
+      const int pre = incl - cnt;
+      n = min(uniform(__builtin_amdgcn_readlane(incl, kWave - 1)), kMaxChunkRows);
+      for (int p = wv; p < npairs; p += kOW) {
+        const uint64_t kb = (uint64_t)L.pm[4 * p] | ((uint64_t)L.pm[4 * p + 1] << 32);
+        const uint64_t cb = (uint64_t)L.pm[4 * p + 2] | ((uint64_t)L.pm[4 * p + 3] << 32);
+        const int q0p = __builtin_amdgcn_readlane(pre, p);
+        if ((kb >> lane) & 1ull) {
+          const int o = g * T + p / nsub, sb = p - (p / nsub) * nsub;
+          const uint32_t row = (uint32_t)(o * R + sb * kWave + lane);
+          const int q = q0p + __popcll(kb & lanes_below(lane));
+          if (q < kMaxChunkRows) L.dent[q] = row | (((cb >> lane) & 1ull) ? 0x80000000u : 0u);
+        }
       }
     }
     const int lo = (n * m) / T, hi = (n * (m + 1)) / T;  // this member's gate/up positions
@@ -946,6 +994,12 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     }
     __syncthreads();
     SI_TRACE_MARK(4);
+    // list form: the proof that every block has read the call counter, by the
+    // finishing wave of the census block alone (the others go on)
+    if (kList && blk == cblk && uniform(wv) == kFin) {
+      census_part(a.pub, P, lane, kWave, tag, a.hdr);
+      if (lane == 0) advance_epoch(a.hdr, epoch);
+    }
 
     // ---- 2. gate/up: wave w takes position lo + w, then the next position
     // no wave has taken yet, and for each its W_gate row and (for confident rows, or without actual
@@ -1736,9 +1790,10 @@ static hipError_t owned_b(const LayerCall& c, hipStream_t s) {
     const int k = c.k, d = c.d;
     const WsLayout L = ws_layout(k, c.b);
     char* base = static_cast<char*>(c.ws);
-    const int mode = c.i8 ? kModeInt8 : c.h != nullptr ? kModeBlock : kModePlain;
+    const int mode = c.i8 ? kModeInt8 : c.h != nullptr ? kModeBlock : c.idx_in != nullptr ? kModeList : kModePlain;
     const int P = mode == kModeInt8    ? owned_blocks<BM, NU, kModeInt8>()
                   : mode == kModeBlock ? owned_blocks<BM, NU, kModeBlock>()
+                  : mode == kModeList  ? owned_blocks<BM, NU, kModeList>()
                                        : owned_blocks<BM, NU, kModePlain>();
     if (P < 1) return hipErrorInvalidConfiguration;
     OwnedArgs a;
@@ -1751,6 +1806,8 @@ static hipError_t owned_b(const LayerCall& c, hipStream_t s) {
     a.sd = c.s_down;
     a.x = c.x;
     a.mask_in = c.mask_in;
+    a.idx_in = c.idx_in;
+    a.n_in = c.n_in;
     a.k = k;
     a.d = d;
     a.b = c.b;
@@ -1762,6 +1819,10 @@ static hipError_t owned_b(const LayerCall& c, hipStream_t s) {
     a.R = owned_rows_per_block(k, P, a.tiles);
     a.groups = min(P / a.tiles, (k + a.R * a.tiles - 1) / (a.R * a.tiles));
     a.nsub = (a.R + kWave - 1) / kWave;
+    if (mode == kModeList) {  // slices of the list over all whole groups, no rows of a block's own
+      a.groups = P / a.tiles;
+      a.nsub = 0;
+    }
     a.mask = c.mask;
     a.idx = c.idx;
     a.n_out = c.n_out;
@@ -1782,12 +1843,15 @@ static hipError_t owned_b(const LayerCall& c, hipStream_t s) {
       if (a.tiles * a.R > kWideGroupRows) {
         const int Pw = mode == kModeInt8    ? owned_blocks<1, NU, kModeInt8, true>()
                        : mode == kModeBlock ? owned_blocks<1, NU, kModeBlock, true>()
+                       : mode == kModeList  ? owned_blocks<1, NU, kModeList, true>()
                                             : owned_blocks<1, NU, kModePlain, true>();
         if (Pw != P) return hipErrorInvalidConfiguration;
         if (mode == kModeInt8)
           k_owned<1, NU, kModeInt8, true><<<P, kOT, lds, s>>>(a);
         else if (mode == kModeBlock)
           k_owned<1, NU, kModeBlock, true><<<P, kOT, lds, s>>>(a);
+        else if (mode == kModeList)
+          k_owned<1, NU, kModeList, true><<<P, kOT, lds, s>>>(a);
         else
           k_owned<1, NU, kModePlain, true><<<P, kOT, lds, s>>>(a);
         launched = true;
@@ -1798,12 +1862,14 @@ static hipError_t owned_b(const LayerCall& c, hipStream_t s) {
         k_owned<BM, NU, kModeInt8, false><<<P, kOT, lds, s>>>(a);
       else if (mode == kModeBlock)
         k_owned<BM, NU, kModeBlock, false><<<P, kOT, lds, s>>>(a);
+      else if (mode == kModeList)
+        k_owned<BM, NU, kModeList, false><<<P, kOT, lds, s>>>(a);
       else
         k_owned<BM, NU, kModePlain, false><<<P, kOT, lds, s>>>(a);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !c.counters || !c.y) return e;
-    return launch_sum_counts(a.counts, P, c.n_out, k, c.counters, s);
+    return launch_sum_counts(a.counts, P, mode == kModeList ? c.n_in : c.n_out, k, c.counters, s);
   }
 }
 
@@ -1828,11 +1894,24 @@ bool owned_supported(int k, int d, int b) {
   return tiles * nsub <= kMaxPairs && tiles * R <= kMaxChunkRows;
 }
 
+// The list form: each block's share as above, the list's slices (over all
+// whole groups) in the LDS list; k as far as the other forms where the whole
+// groups cover the grid.
+bool list_supported(int k, int d, int b) {
+  const int P = owned_blocks_for(d, b);
+  const int tiles = (d + kTile - 1) / kTile;
+  if (P < 1 || P < tiles) return false;
+  const int groups = P / tiles;
+  return (k + P - 1) / P <= kMaxOwnRows && (k + groups - 1) / groups <= kMaxChunkRows;
+}
+
 hipError_t launch_owned(const LayerCall& c, hipStream_t s) {
   const int d = c.d, b = c.b;
 #define LAUNCH(BM, NU) owned_b<BM, NU>(c, s)
   SI_LAYER_DISPATCH(LAUNCH)
 #undef LAUNCH
 }
+#undef SI_LAYER_DISPATCH
+#undef SI_NU_DISPATCH
 
 }  // namespace si

@@ -29,7 +29,6 @@ constexpr uint32_t kErrRow = 4u;           // kept-row index outside [0, k)
 
 // Where the last MLP call left h3 (Eq. (1) step 3) in the workspace.
 constexpr uint32_t kH3ByRow = 1u;       // h3e[row][b]: this call's tag | fp32 bits
-constexpr uint32_t kH3ByPos = 2u;       // h3e[list position][b]: this call's tag | fp32 bits
 constexpr uint32_t kH3PlainByRow = 3u;  // h3[row][b] fp32, valid on the kept rows
 
 constexpr int kGateUpMaxBlocks = 2048;     // grid cap of the list-driven gate/up kernel
@@ -47,7 +46,7 @@ struct WsLayout {
   size_t upflag;  // uint8 [k] 1 where the W_up row was read
   size_t lmask;   // uint64 [groups][4] single-kernel kept / confident masks
   size_t zflag;   // uint64 [64] single-kernel "tile of y zeroed" flags
-  size_t alive;   // uint64 [kMaxLayerBlocks] single-kernel "this block has read the call counter" words
+  size_t spare;   // uint64 [kMaxLayerBlocks], not used (callers' workspaces keep their size)
   size_t opub;    // uint64 [kMaxLayerBlocks][kOwnPubStride] row-owning kernel: masks and count per block
   size_t h3;      // float [k][b] h3 per row (valid on kept rows)
   size_t h3e;     // uint64 [groups][64][b] single-kernel h3 exchange words
@@ -73,8 +72,8 @@ __host__ __device__ inline WsLayout ws_layout(int k, int b) {
   L.upflag = L.mask + align256((size_t)k);
   L.lmask = L.upflag + align256((size_t)k);
   L.zflag = L.lmask + align256(groups * 4 * sizeof(uint64_t));
-  L.alive = L.zflag + align256(64 * sizeof(uint64_t));
-  L.opub = L.alive + align256(kMaxLayerBlocks * sizeof(uint64_t));
+  L.spare = L.zflag + align256(64 * sizeof(uint64_t));
+  L.opub = L.spare + align256(kMaxLayerBlocks * sizeof(uint64_t));
   L.h3 = L.opub + align256((size_t)kMaxLayerBlocks * kOwnPubStride * sizeof(uint64_t));
   L.h3e = L.h3 + align256((size_t)k * b * sizeof(float));
   L.total = L.h3e + align256(groups * kRowGroup * (size_t)b * sizeof(uint64_t));

@@ -51,10 +51,10 @@ hipError_t launch_predict_gate_up(const uint32_t* signs, const uint16_t* w_gate,
 hipError_t launch_down(const uint16_t* w_down_t, int k, int d, int b, const int32_t* idx, const int32_t* n_active,
                        float* y, void* ws, int slots, uint32_t flags, int32_t* counters, hipStream_t s);
 
-// The path of one layer in one kernel (layer.hip).  The kept rows come from
+// The path of one layer in one kernel (owned.hip).  The kept rows come from
 // the packed signs (predict: signs set, mask_in and idx_in NULL), from a
 // caller's mask (mask_in set) or from a caller's list (idx_in and n_in set);
-// y NULL runs the predictor alone.  Only valid when layer_supported(k, d, b).
+// y NULL runs the predictor alone.
 struct LayerCall {
   const uint32_t* signs = nullptr;
   const uint16_t* w_gate = nullptr;
@@ -86,13 +86,12 @@ struct LayerCall {
   const float* s_up = nullptr;
   const float* s_down = nullptr;
 };
-bool layer_supported(int k, int d, int b);
-hipError_t launch_layer(const LayerCall& c, hipStream_t s);
 
-// The row-owning single-launch kernel (owned.hip) for predict and mask
-// calls (idx_in must be NULL); idx, mask and n_out are each written when not
-// NULL.  Only valid when owned_supported(k, d, b).
+// The single-launch kernel (owned.hip); idx, mask and n_out are each written
+// when not NULL.  Only valid when owned_supported(k, d, b), with idx_in when
+// list_supported(k, d, b).
 bool owned_supported(int k, int d, int b);
+bool list_supported(int k, int d, int b);
 hipError_t launch_owned(const LayerCall& c, hipStream_t s);
 
 // Per-row h3 of the last MLP call made with workspace `ws` -> out[k][b]
@@ -104,9 +103,6 @@ hipError_t launch_read_probe(const void* buf, size_t bytes, uint32_t* sink, hipS
 
 // mask -> ascending kept list and count (single block).
 hipError_t launch_compact(const uint8_t* mask, int k, int32_t* idx, int32_t* n_out, hipStream_t s);
-
-// ascending kept list and count -> [k] mask (single block).
-hipError_t launch_list_to_mask(const int32_t* idx, const int32_t* n_in, int k, uint8_t* mask, hipStream_t s);
 
 // Sparse gate/up (+ReLU, product, actual sparsity) and sparse down.
 hipError_t launch_sparse_mlp(const uint16_t* w_gate, const uint16_t* w_up, const uint16_t* w_down_t,
