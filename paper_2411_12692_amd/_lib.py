@@ -91,10 +91,9 @@ def load() -> ctypes.CDLL:
 
 def call(name: str, *args) -> None:
     """Call an entry point that returns si_status; raise on failure."""
-    lib = load()
-    st = getattr(lib, name)(*args)
+    st = getattr(_lib or load(), name)(*args)
     if st != SI_OK:
-        raise SparseInferError(st, lib.si_last_error().decode())
+        raise SparseInferError(st, last_error())
 
 
 def status(name: str, *args) -> int:
