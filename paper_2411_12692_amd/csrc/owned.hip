@@ -116,7 +116,10 @@ static_assert(kODN * kMaxB <= kWave, "a wave polls the h3 words of its pieces, o
 // into two fp16 parts (hi + lo), so the products keep fp32 precision for any
 // finite h3.
 constexpr int kMRows = 32;                // rows per chunk
-constexpr int kMInflight = 3;             // chunks whose pieces are in flight (3-4 tokens; one more with 5-8)
+// chunks whose pieces are in flight (us per 7B call, 4 / 8 tokens and INT8 with 8:
+// 2 23.6 / 41.1 / 32.4, 3 23.9 / 41.2 / 33.0; 24.0 / 42.0 / 35.7 while each
+// chunk waited for every request, see below)
+constexpr int kMInflight = 2;
 constexpr int kMPitch = kTile * 2 + 32;   // bytes per row of a chunk in LDS (padded against bank conflicts)
 constexpr int kMTok = 16;                 // tokens of the MFMA (b <= 8 used)
 static_assert(kMRows == 4 * kOW, "each wave stages 4 rows of a chunk (16 lanes per row)");
@@ -216,6 +219,7 @@ __device__ inline void poll_words(const uint64_t* const (&p)[N], int n, uint32_t
     if (i < n) pending |= 1u << i;
   }
   long spins = 0;
+#pragma unroll 1
   while (pending) {
     uint64_t v[N];
 #pragma unroll
@@ -1332,9 +1336,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         mdone = true;
         MfmaLds<BM>& M = *reinterpret_cast<MfmaLds<BM>*>(L.mf_raw);
         const int nch = (dN + kMRows - 1) / kMRows;
-        // chunks in flight: 4 with 5-8 tokens (the fused 8-token call 58.6 ->
-        // 57.7 us), 3 with 3-4 (4 made the 4-token call 0.4 us slower)
-        constexpr int kMI = BM >= 8 ? kMInflight + 1 : kMInflight;
+        constexpr int kMI = kMInflight;
         // pieces: the thread stages row 4 wv + lane / 16 of each chunk, its
         // 16-byte units lane % 16 + 16 j (j < 4) of the tile
         const int prow = 4 * wv + (lane >> 4), pslot = lane & 15;
@@ -1347,21 +1349,24 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         static_assert(kMRows * kMaxB / kWave < kOW, "the zero-flag wave reads no h3 words");
         const int tcu = tile * kWave;  // the tile's first 16-byte unit of a row
         typedef typename DP::type PT;
+        // a chunk's requests are the same five in every wave, and none is behind
+        // a branch (the last chunks have code of their own): with a branch
+        // around any of them the compiler no longer knows how many requests are
+        // behind the one it waits for, waits for all, and every chunk takes a
+        // round trip to memory
         auto request = [&](int c, PT(&pc)[4], uint64_t& w) {
           const int q = min(c * kMRows + prow, dN - 1);
           const size_t row = L.dent[q] & 0x7fffffffu;
 #pragma unroll
-          for (int j = 0; j < 4; ++j) pc[j] = DP::load(a.wdt, row, U, min(tcu + pslot + 16 * j, U - 1));
+          for (int j = 0; j < 4; ++j)
+            pc[j] = DP::load(a.wdt, row, U, min(tcu + pslot + 16 * j, U - 1));
           // the first read of the chunk's h3 words goes out right behind its
           // pieces (a poll issued later would wait for every request before it)
-          if (hwave) {
-            const int hq = min(c * kMRows + hrow, dN - 1);
-            w = ld_agent64(a.h3e + (size_t)(L.dent[hq] & 0x7fffffffu) * b + min(htok, b - 1));
-          } else if (zwave && c == 0) {
-            w = ld_agent64(&a.zflag[tile]);
-          }
+          const int hq = min(c * kMRows + hrow, dN - 1);
+          const uint64_t* hp = a.h3e + (size_t)(L.dent[hq] & 0x7fffffffu) * b + min(htok, b - 1);
+          w = ld_agent64(hwave ? hp : &a.zflag[tile]);
         };
-        auto chunk = [&](int c, PT(&pc)[4], uint64_t& w) {
+        auto chunk = [&](int c, PT(&pc)[4], uint64_t& w, auto more) {
           float v = 0.f;
           if (hwave) {
             const int hq = c * kMRows + hrow;
@@ -1401,7 +1406,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
               const int hlf = i / ((kMTok - BM) * kMRows), r = i - hlf * ((kMTok - BM) * kMRows);
               M.bop[hlf][BM + r / kMRows][r % kMRows] = 0;
             }
-          if (c + kMI < nch) request(c + kMI, pc, w);
+          if constexpr (decltype(more)::value) request(c + kMI, pc, w);
           __syncthreads();
           // lane (g = lane / 16, j16 = lane % 16): B = token j16's rows
           // 8 g .. 8 g + 7; A = those rows of column j16 of the block, from
@@ -1431,31 +1436,36 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
           }
           if (c == 0) SI_TRACE_WAVE(4);
         };
-        if constexpr (kMI == 4) {
-          PT p0[4], p1[4], p2[4], p3[4];
-          uint64_t w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-          request(0, p0, w0);
-          if (1 < nch) request(1, p1, w1);
-          if (2 < nch) request(2, p2, w2);
-          if (3 < nch) request(3, p3, w3);
-          for (int c = 0; c < nch; c += kMI) {
-            chunk(c, p0, w0);
-            if (c + 1 < nch) chunk(c + 1, p1, w1);
-            if (c + 2 < nch) chunk(c + 2, p2, w2);
-            if (c + 3 < nch) chunk(c + 3, p3, w3);
+        PT pc[kMI][4];
+        uint64_t hw[kMI];
+        constexpr std::true_type kMore{};
+        constexpr std::false_type kLast{};
+        // the last R chunks, of which the first min(R, kMI) are requested
+        auto tail = [&](int c, auto r) {
+          constexpr int R = decltype(r)::value;
+#pragma unroll
+          for (int i = 0; i < R; ++i) {
+            if (i + kMI < R)
+              chunk(c + i, pc[i % kMI], hw[i % kMI], kMore);
+            else
+              chunk(c + i, pc[i % kMI], hw[i % kMI], kLast);
           }
+        };
+        static_assert(kMI == 2, "the cases below");
+        request(0, pc[0], hw[0]);
+        if (nch == 1) {
+          tail(0, std::integral_constant<int, 1>{});
         } else {
-          PT p0[4], p1[4], p2[4];
-          uint64_t w0 = 0, w1 = 0, w2 = 0;
-          static_assert(kMI == 3, "three chunks in flight");
-          request(0, p0, w0);
-          if (1 < nch) request(1, p1, w1);
-          if (2 < nch) request(2, p2, w2);
-          for (int c = 0; c < nch; c += kMI) {
-            chunk(c, p0, w0);
-            if (c + 1 < nch) chunk(c + 1, p1, w1);
-            if (c + 2 < nch) chunk(c + 2, p2, w2);
+          request(1, pc[1], hw[1]);
+          int c = 0;
+          for (; nch - c >= 2 * kMI; c += kMI) {
+#pragma unroll
+            for (int i = 0; i < kMI; ++i) chunk(c + i, pc[i], hw[i], kMore);
           }
+          if (nch - c == 2)
+            tail(c, std::integral_constant<int, 2>{});
+          else
+            tail(c, std::integral_constant<int, 3>{});
         }
         n_down = wv == 0 ? dN : 0;
       }
