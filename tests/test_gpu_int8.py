@@ -241,6 +241,37 @@ def test_int8_tokens_4x4_windows(k, d, b, gated):
     check(c, m, y, cnt)
 
 
+@pytest.mark.parametrize("d,R,b,gated,flags", [(512, 200, 3, True, 0), (512, 200, 4, True, si.SI_NO_SPECULATION),
+                                               (512, 200, 8, True, 0), (512, 200, 8, True, si.SI_NO_SPECULATION),
+                                               (512, 200, 5, True, si.SI_NO_AS), (512, 200, 8, False, 0),
+                                               (512, 200, 3, False, si.SI_NO_SPECULATION), (1152, 104, 6, True, 0)])
+def test_int8_tokens_large_shares(d, R, b, gated, flags):
+    """3-8 tokens with shares of more than 32 rows per block: its waves take
+    their second and later fours from the block's counter (32 rows are the
+    first fours of the 8 waves), the last four being partly empty, without
+    speculation each with its late W_up rows.  A group of blocks keeps a
+    different number of its rows: at d = 512 (one block per group) 0 to 200
+    rows, so 0 to 7 chunks of the down-projection as well, at d = 1152 (three
+    blocks) up to 312, shares of up to 104."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T = (d + 511) // 512
+    groups, rows = cus // T, T * R
+    k = groups * rows
+    counts = [0, 1, 3, 31, 32, 33, 34, 35, 36, 37, 47, 48, 63, 64, 65, 66, 67, 68, 96, 97, 128, 161, 199, 200, 288, 301,
+              rows]
+    rng = np.random.default_rng(1000 * b + d + flags)
+    mask = np.zeros((groups, rows), np.uint8)
+    for g in range(groups):
+        mask[g, rng.permutation(rows)[: min(counts[g % len(counts)], rows)]] = 1
+    mask = mask.reshape(-1)
+    c = I8Case(rand_bits(rng, (k, d)), rand_bits(rng, (k, d)) if gated else None, rand_bits(rng, (d, k)),
+               rand_bits(rng, (b, d)), max_batch=b)
+    assert si._lib.load().si_single_launch(k, d, b) == 1
+    y, cnt = c.layer.sparse_mlp(to_dev(c.x), torch.from_numpy(mask).to(DEV), flags=flags, counters=True)
+    torch.cuda.synchronize()
+    check(c, mask, y, cnt, flags)
+
+
 @pytest.mark.parametrize("k,d,gated", [(9000, 8192, True), (40000, 2048, True), (20000, 4096, False)])
 def test_int8_one_token_large_groups(k, d, gated):
     """One token with groups of more than 512 rows (T = ceil(d / 512) blocks
