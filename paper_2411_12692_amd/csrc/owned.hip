@@ -662,6 +662,14 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       // requests travel together (a load-store loop waits once per unit: 2
       // us of 64 KB with 8 tokens).
       constexpr int kXW = 16 * kSU, JW = (BM * kXW + kWave - 1) / kWave;
+      // a count reads as 16-byte words the sign bytes that other lanes of its
+      // wave wrote: a wave's LDS operations complete in order, and this keeps the
+      // compiler from moving one past the other (no instruction of its own)
+      auto signs_written = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      };
       u32x4 xv[JW];
 #pragma unroll
       for (int j = 0; j < JW; ++j) {
@@ -684,9 +692,13 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         }
         // (one token: here; in a pass after the loop the 7B call took 12.23
         // instead of 12.01 us)
-        if (BM == 1 && j == JW - 1 && predict && Rb > 0) count_token(0);
+        if (BM == 1 && j == JW - 1 && predict && Rb > 0) {
+          signs_written();
+          count_token(0);
+        }
       }
       if (BM > 1 && predict && Rb > 0) {
+        signs_written();
 #pragma unroll
         for (int t = 0; t < BM; ++t) count_token(t);
       }
