@@ -271,6 +271,7 @@ def time_steps(step, steps, warmup):
     import torch
 
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())  # inputs and zero-filled workspaces are made there
     with torch.cuda.stream(stream):
         for i in range(warmup):
             step(i)
@@ -325,6 +326,7 @@ def measured_read_peak(si, dev, total_bytes=4 << 30, slice_bytes=32 << 20):
     buf = torch.zeros(total_bytes, dtype=torch.uint8, device=dev)
     sink = torch.zeros(4, dtype=torch.int32, device=dev)
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
 
     def probe(off, n):
         si._lib.call("si_read_bandwidth_probe", ctypes.c_void_p(buf.data_ptr() + off), n,
@@ -369,6 +371,7 @@ def graph_us(fn, calls, reps=4, warm=1):
     import torch
 
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(stream):
         for i in range(min(calls, 16)):
             fn(i)
@@ -566,6 +569,7 @@ def report_stacks(args, si, synth, dev):
             stream = torch.cuda.Stream()
             g = torch.cuda.CUDAGraph()
             reset()
+            stream.wait_stream(torch.cuda.current_stream())
             with torch.cuda.stream(stream):
                 token(mlp)
             torch.cuda.synchronize()
@@ -878,6 +882,7 @@ def main():
     M = args.launches
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(M)]
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(stream):
         torch.cuda._sleep(int(2.4e9 * 0.02 * max(1, M / 256)))
         for i in range(M):

@@ -99,6 +99,7 @@ def main() -> None:
                 f"pool of {L} layers")
 
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())  # the layers and zero-filled workspaces are made there
     n_calls = 2 * L
     with torch.cuda.stream(stream):
         for i in range(n_calls):

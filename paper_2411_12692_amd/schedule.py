@@ -118,6 +118,7 @@ def calibrate_stack(layers, xs_per_layer: Sequence[Sequence[torch.Tensor]], targ
 
 def _graph_time_us(fns: Sequence[Callable[[], None]], reps: int) -> float:
     stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())  # inputs and zero-filled workspaces are made there
     with torch.cuda.stream(stream):
         for f in fns:
             f()
