@@ -653,6 +653,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         const int i = tid + j * kOT, t = i / XS, u = i - t * XS;
         if (i < BM * XS && !(t < b && u < U)) L.xs[t * XP + u] = u32x4{0, 0, 0, 0};
       }
+      SI_TRACE_MARK(1);
     } else {
       // the wave stages the tokens' 16-byte units that its own sign units
       // cover (kXW of each token), so that it forms their sign bytes and
@@ -690,6 +691,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
           L.xs[t * XP + u] = v;
           if (predict && u < U) reinterpret_cast<uint8_t*>(L.xw)[t * 4 * W + u] = (uint8_t)sign_byte(v);
         }
+        if (j == JW - 1) SI_TRACE_MARK(1);
         // (one token: here; in a pass after the loop the 7B call took 12.23
         // instead of 12.01 us)
         if (BM == 1 && j == JW - 1 && predict && Rb > 0) {
@@ -783,6 +785,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
       const float v = wave_total(ss[t]);
       if (lane == 0) L.nsum[wv][t] = v;
     }
+    SI_TRACE_MARK(1);
   }
   if constexpr (block_mode) {  // (the sign bytes are other waves' there; with
     // the units of h dealt like the sign units, and so without this barrier, the
@@ -838,7 +841,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
   // load left outstanding into the loop below would make the compiler wait
   // for every outstanding request, stores included, inside it)
   bool mkeep = mbyte != 0;
-  SI_TRACE_MARK(1);
+  SI_TRACE_MARK(2);
   if constexpr (kList) {  // this block has read the call counter
     if (tid == 0) st_agent64(&a.pub[(size_t)blk * kOwnPubStride + kCountWord], tagged(tag, 0u));
   }

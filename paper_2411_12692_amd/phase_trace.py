@@ -10,14 +10,16 @@ launch of each graph replay this prints, per point, the median, p10, p90
 and maximum over blocks (or waves) of the time since the earliest block
 started, each the median over several replays.
 
-Usage: ``python -m paper_2411_12692_amd.phase_trace [--batch B] [--int8] [--shape 7b|13b] [--replays N]``
+Usage: ``python -m paper_2411_12692_amd.phase_trace [--batch B] [--fused] [--int8] [--shape 7b|13b] [--replays N]``
 
 Workloads: one token: the fused call (predict + MLP) on 16 planted 7B-shaped
 layers (d = 4096, k = 11008, s = 0.9, alpha = 1), as ``bench.py`` times it
 (``--int8``: the same layers quantized to INT8, ``bench.py --mlp int8``;
 ``--shape 13b``: 13B-shaped layers, d = 5120, k = 13824, s = 0.88,
 ``bench.py --shape 13b``); B tokens: the mask call over the union of the
-tokens' planted active sets of 8 7B-shaped layers (``bench.py --batch B``).
+tokens' planted active sets of 8 7B-shaped layers (``bench.py --batch B``), or
+with ``--fused`` the fused call on the same tokens, which predicts its rows
+itself; either with INT8 weights too.
 """
 
 from __future__ import annotations
@@ -30,8 +32,8 @@ import numpy as np
 
 BLOCK_MARKS = {
     0: "block start",
-    1: "tokens staged, x signs formed",
-    2: "first popcount pass done",
+    1: "wave 0's token units staged",
+    2: "first barrier passed (counts in)",
     3: "own kept rows published",
     4: "group list formed",
     6: "wave 0's gate/up rows done",
@@ -54,7 +56,8 @@ def main() -> None:
     ap = argparse.ArgumentParser()
     ap.add_argument("--batch", type=int, default=1)
     ap.add_argument("--replays", type=int, default=8)
-    ap.add_argument("--int8", action="store_true", help="INT8 weights (one token)")
+    ap.add_argument("--int8", action="store_true", help="INT8 weights")
+    ap.add_argument("--fused", action="store_true", help="several tokens: the fused call instead of the mask call")
     ap.add_argument("--shape", choices=("7b", "13b"), default="7b", help="layer shape (one token)")
     args = ap.parse_args()
     if args.shape != "7b" and args.batch != 1:
@@ -74,29 +77,24 @@ def main() -> None:
     D, K, S, cfg = (5120, 13824, 0.88, 4) if args.shape == "13b" else (4096, 11008, 0.9, 2)
     b = args.batch
     L = 16 if b == 1 else 8
-    if b == 1:
-        pls = [synth.planted_layer(D, K, S, config=cfg, layer=l, device=dev) for l in range(L)]
-        if args.int8:
-            layers = [si.Int8MLPLayer(p.w_gate, p.w_up, p.w_down) for p in pls]
-        else:
-            layers = [si.MLPLayer(p.w_gate, p.w_up, p.w_down) for p in pls]
-        xs = [p.x for p in pls]
-        y = torch.empty(1, D, dtype=torch.float32, device=dev)
+    cfg = cfg if b == 1 else 5
+    pls = [synth.planted_layer(D, K, S, config=cfg, layer=l, device=dev) for l in range(L)]
+    make = si.Int8MLPLayer if args.int8 else si.MLPLayer
+    layers = [make(p.w_gate, p.w_up, p.w_down, max_batch=b) for p in pls]
+    xs = [synth.batch_tokens(p, b, config=cfg, layer_id=l) for l, p in enumerate(pls)]
+    what = f"{args.shape.upper()} layer (d={D}, k={K}){', INT8 weights' if args.int8 else ''}, "
+    if b == 1 or args.fused:
+        y = torch.empty(b, D, dtype=torch.float32, device=dev)
 
         def call(i):
             layers[i % L](xs[i % L], 1.0, y=y)
-        what = (f"fused call, {args.shape.upper()} layer (d={D}, k={K}){', INT8 weights' if args.int8 else ''}, "
-                f"planted s={S}, alpha=1, 1 token, pool of {L} layers")
+        what = f"fused call, {what}planted s={S}, alpha=1, {b} token{'s' if b > 1 else ''}, pool of {L} layers"
     else:
-        pls = [synth.planted_layer(D, K, 0.9, config=5, layer=l, device=dev) for l in range(L)]
-        layers = [si.MLPLayer(p.w_gate, p.w_up, p.w_down, max_batch=b) for p in pls]
-        xs = [synth.batch_tokens(p, b, config=5, layer_id=l) for l, p in enumerate(pls)]
-        ms = [synth.batch_union_mask(p, b, config=5, layer_id=l) for l, p in enumerate(pls)]
+        ms = [synth.batch_union_mask(p, b, config=cfg, layer_id=l) for l, p in enumerate(pls)]
 
         def call(i):
             layers[i % L].sparse_mlp(xs[i % L], mask=ms[i % L])
-        what = (f"mask call over the union of {b} tokens' planted active sets, 7B layer (d={D}, k={K}), s=0.9, "
-                f"pool of {L} layers")
+        what = f"mask call over the union of {b} tokens' planted active sets, {what}s={S}, pool of {L} layers"
 
     stream = torch.cuda.Stream()
     stream.wait_stream(torch.cuda.current_stream())  # the layers and zero-filled workspaces are made there
