@@ -222,7 +222,8 @@ si_status si_predict(const uint32_t* signs, int k, int d, const uint16_t* x, int
  *                  NULL, in which case the kept list is built from it.
  *   active_idx, n_active : kept rows in ascending order and their count, as
  *                  written by si_predict (device memory).  Either both or
- *                  neither may be NULL.
+ *                  neither may be NULL.  Each row at most once: a row listed
+ *                  more than once is added to y, and counted, once per entry.
  *   y            : [b][d] float, overwritten.
  *   flags        : 0, SI_NO_AS, SI_NO_SPECULATION or both.
  *   counters     : [3] int32 or NULL: rows whose W_gate, W_up and W_down^T
@@ -242,7 +243,9 @@ si_status si_sparse_mlp(const uint16_t* w_gate, const uint16_t* w_up, const uint
  * current device: at most 256 rows of W_gate per compute unit (k <= 65536 on
  * a 256-CU MI355X) and one block with 96-160 KB of LDS resident on every
  * compute unit; 0 if they take the multi-launch path (same results) or the
- * shapes are invalid.  Host-only query.
+ * shapes are invalid.  (si_sparse_mlp over an active_idx is a single launch up
+ * to 256 rows per compute unit also where d makes the answer 0 a few rows
+ * earlier.)  Host-only query.
  */
 int si_single_launch(int k, int d, int b);
 

@@ -86,3 +86,27 @@ def test_list_rows_out_of_range(b):
     lst[[0, 17, 200, 399]] = [-1, k, 1 << 24, -(1 << 31)]
     L.check(lst, bad=True)
     L.check(lst[1:17])
+
+
+@pytest.mark.parametrize("b", [1, 3, 8])
+def test_list_repeated_rows(b):
+    """Each entry of the list counts, also one that repeats a row: next to it
+    in an ascending list, or in another group's slice."""
+    k = 1200
+    L = Layer(k, 1024, b, True, 50 + b)
+    rng = np.random.default_rng(b)
+    rows = np.sort(rng.permutation(k)[:300])
+    twice = rows[::7]
+    once, again = np.zeros(k, np.uint8), np.zeros(k, np.uint8)
+    once[rows] = 1
+    again[twice] = 1
+    y1 = oracle.sparse_mlp(L.wg, L.wu, L.wd, L.x, once)["y"]
+    yr = y1 + oracle.sparse_mlp(L.wg, L.wu, L.wd, L.x, again)["y"]
+    for lst in (np.sort(np.concatenate([rows, twice])), np.concatenate([rows, twice])):
+        n = len(lst)
+        y, cnt = L.g.sparse_mlp(L.xd, active_idx=dev(lst.astype(np.int32)), n_active=dev(np.array([n], np.int32)),
+                                counters=True)
+        torch.cuda.synchronize()
+        assert workspace_ok(L.g.workspace)
+        assert np.abs(y.cpu().numpy() - yr).max() <= 1e-4 * np.abs(yr).max()
+        assert cnt.cpu().numpy()[0] == n
