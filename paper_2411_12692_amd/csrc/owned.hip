@@ -318,7 +318,7 @@ __device__ inline void i8_to_h16(u32x4 v, u32x4& lo, u32x4& hi) {
 // Dot products of one or two INT8 rows held as (NU + 1) / 2 16-byte units
 // per lane (unit lane + 64 j: 16 values, the tokens' fp16 units 2u and
 // 2u + 1) with the BM tokens in LDS; unscaled, wave-uniform results.
-template <int BM, int NU, bool TWO>
+template <int BM, int NU, int XP, bool TWO>
 __device__ inline void row_dots_i8(const u32x4 (&v)[(NU + 1) / 2], const u32x4 (&w)[(NU + 1) / 2],
                                    const u32x4* xs, int U8, int lane, float (&o1)[BM], float (&o2)[BM]) {
   constexpr int NU8 = (NU + 1) / 2;
@@ -334,7 +334,7 @@ __device__ inline void row_dots_i8(const u32x4 (&v)[(NU + 1) / 2], const u32x4 (
     if constexpr (TWO) i8_to_h16(w[j], wl, wh);
 #pragma unroll
     for (int t = 0; t < BM; ++t) {
-      const u32x4 x0 = xs[t * (NU * kWave) + 2 * uc], x1 = xs[t * (NU * kWave) + 2 * uc + 1];
+      const u32x4 x0 = xs[t * XP + 2 * uc], x1 = xs[t * XP + 2 * uc + 1];
       const float s1 = dot8(vh, x1, dot8(vl, x0, a1[t]));
       a1[t] = u < U8 ? s1 : a1[t];
       if constexpr (TWO) {
@@ -342,6 +342,7 @@ __device__ inline void row_dots_i8(const u32x4 (&v)[(NU + 1) / 2], const u32x4 (
         a2[t] = u < U8 ? s2 : a2[t];
       }
     }
+    if constexpr (BM >= 4) __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int t = 0; t < BM; ++t) {
@@ -1038,8 +1039,18 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // tokens: 99 -> 93 us).  An instance of its own: the branch alone made
     // small gated calls 0.3 us slower.
     const int up_rows = kPairs && hi - lo >= 2 * kOW ? 2 : 1;
+    // INT8 weights, 3-4 tokens: up to as many rows (W_gate's and W_up's) as
+    // waves, the matrix cores' four rows to a wave leave most waves idle and
+    // the rows go one to a wave on the vector ALU (7B mask call, 3 tokens, s =
+    // 0.985, two rows a block: 11.79 -> 11.10 us; d = 2048, k = 5632 without
+    // W_up, 4 tokens, s = 0.95: 12.47 -> 11.76).  Above that the matrix cores
+    // win (2048 x 5632, 3 tokens, s = 0.9, six rows: 12.55, else 13.87); with 5-8
+    // tokens they do at every share (s = 0.993: 17.3, else 17.7).  Dealing them
+    // fewer than four rows a wave was slower at every share (7B, 4 tokens, s =
+    // 0.97: 16.35 -> 18.16).
+    const bool mfma_up = kMfmaUp && (BM > 4 || (gated ? 2 : 1) * (hi - lo) > kOW);
     if (tid == 0) {
-      L.gpos = lo + (kMfmaUp ? kUpRows : up_rows) * kOW;
+      L.gpos = lo + (mfma_up ? kUpRows : up_rows) * kOW;
       L.dpos = 0;
       L.issued = 0;
       L.wsum[0] = 0;
@@ -1061,172 +1072,175 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // its own (no block barrier) and publishes h3 per row and token.
     int n_up = 0;
     if constexpr (kMfmaUp) {
-      // INT8 weights, 3-8 tokens, on the matrix cores: a wave takes 4 rows at a
-      // time and multiplies them with 4 tokens per 4x4x4 MFMA, whose 16
-      // blocks take 16 pieces of the rows.  A request reads 256 bytes of each of
-      // the 4 rows (lane 4 p + n: the 16-byte piece p of row n), which is the
-      // MFMA's layout as it comes; the tokens come from LDS in the same
-      // layout, once for W_gate and W_up.  On the vector ALU (a row pair per
-      // wave, converted and multiplied with every token in turn) the phase
-      // was issue bound: the 8-token 7B call took 46.4 us, with this 35.9 (gate/up
-      // done at 23.8 us, now 15-18, of which the 45 MB of rows take 8).  fp16
-      // rows stay on the vector ALU: their phase is bound by the rows'
-      // bytes, and whole rows requested 1 KB at a time stream better than the
-      // 4 x 256 bytes here (4 tokens 24.2 us, this way 26.4; 8 tokens 41.7 and
-      // 41.1; with the rows turned around in registers instead 26.5 and 42.2).
-      typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-      typedef float f4 __attribute__((ext_vector_type(4)));
-      typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-      constexpr int TG = BM / 4;                     // token groups
-      constexpr int kWinMax = 2 * NU;                // 256-byte windows of a row, at most
-      const int rowu = d >> 4;                       // 16-byte units of a row
-      const int nwin = (rowu + 15) >> 4;
-      const int qp = lane >> 2, qn = lane & 3;
-      const u32x4* xa = &L.xs[qn * OwnedLds<BM, NU>::kStride + 2 * qp];
-      constexpr int kTG = 4 * OwnedLds<BM, NU>::kStride;  // from a token to the next group's
-      struct Acc {
-        f4 v[TG][2];  // token 4 tg + i of the lane's row, over the lane's pieces (two halves each)
-      };
-      auto mfma = [](u32x4 w, u32x4 x, f4(&c)[2]) {
-        c[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.x, x.y}),
-                                                  __builtin_bit_cast(h4, u2{w.x, w.y}), c[0], 0, 0, 0);
-        c[1] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.z, x.w}),
-                                                  __builtin_bit_cast(h4, u2{w.z, w.w}), c[1], 0, 0, 0);
-      };
-      // the tokens of window w in the MFMA's layout: the two 8-value halves of
-      // the lane's piece
-      struct Tok {
-        u32x4 v[TG][2];
-      };
-      auto tokens = [&](int w) -> Tok {
-        Tok x;
-#pragma unroll
-        for (int t = 0; t < TG; ++t) {
-          x.v[t][0] = xa[t * kTG + 32 * w];
-          x.v[t][1] = xa[t * kTG + 32 * w + 1];
-        }
-        return x;
-      };
-      // the products of a window of one or two matrices
-      auto window = [&](const Tok& x, u32x4 vg, u32x4 vu, Acc& ag, Acc& au, auto two) {
-        constexpr bool kTwo = decltype(two)::value;
-        u32x4 gl, gh, ul, uh;
-        i8_to_h16(vg, gl, gh);
-        if constexpr (kTwo) i8_to_h16(vu, ul, uh);
-#pragma unroll
-        for (int t = 0; t < TG; ++t) {
-          mfma(gl, x.v[t][0], ag.v[t]);
-          mfma(gh, x.v[t][1], ag.v[t]);
-          if constexpr (kTwo) {
-            mfma(ul, x.v[t][0], au.v[t]);
-            mfma(uh, x.v[t][1], au.v[t]);
-          }
-        }
-      };
-      // the whole rows, kDepth windows of them in flight: a window's registers
-      // take the request kDepth windows on as soon as it is multiplied (the
-      // scheduling barriers keep the request there, and the tokens one window
-      // ahead).  Windows past the row's end request its last unit again and
-      // are left out of the products; in the last window of a row of an odd
-      // number of 128-byte lines the tokens' units past d are zero.
-      constexpr int kDepth = kWinMax < 8 ? kWinMax : 8;
-      auto rows = [&](const u32x4* pg, const u32x4* pu, Acc& ag, Acc& au, auto two) {
-        constexpr bool kTwo = decltype(two)::value;
-        u32x4 vg[kDepth], vu[kTwo ? kDepth : 1];
-        auto request = [&](int i, int w) {
-          const int u = min(16 * w + qp, rowu - 1);
-          vg[i] = load_nt(pg + u);
-          if constexpr (kTwo) vu[i] = load_nt(pu + u);
+      if (mfma_up) {
+        // INT8 weights, 3-8 tokens, on the matrix cores: a wave takes 4 rows at a
+        // time and multiplies them with 4 tokens per 4x4x4 MFMA, whose 16
+        // blocks take 16 pieces of the rows.  A request reads 256 bytes of each of
+        // the 4 rows (lane 4 p + n: the 16-byte piece p of row n), which is the
+        // MFMA's layout as it comes; the tokens come from LDS in the same
+        // layout, once for W_gate and W_up.  On the vector ALU (a row pair per
+        // wave, converted and multiplied with every token in turn) the phase
+        // was issue bound: the 8-token 7B call took 46.4 us, with this 35.9 (gate/up
+        // done at 23.8 us, now 15-18, of which the 45 MB of rows take 8).  fp16
+        // rows stay on the vector ALU: their phase is bound by the rows'
+        // bytes, and whole rows requested 1 KB at a time stream better than the
+        // 4 x 256 bytes here (4 tokens 24.2 us, this way 26.4; 8 tokens 41.7 and
+        // 41.1; with the rows turned around in registers instead 26.5 and 42.2).
+        typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+        typedef float f4 __attribute__((ext_vector_type(4)));
+        typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+        constexpr int TG = BM / 4;                     // token groups
+        constexpr int kWinMax = 2 * NU;                // 256-byte windows of a row, at most
+        const int rowu = d >> 4;                       // 16-byte units of a row
+        const int nwin = (rowu + 15) >> 4;
+        const int qp = lane >> 2, qn = lane & 3;
+        const u32x4* xa = &L.xs[qn * OwnedLds<BM, NU>::kStride + 2 * qp];
+        constexpr int kTG = 4 * OwnedLds<BM, NU>::kStride;  // from a token to the next group's
+        struct Acc {
+          f4 v[TG][2];  // token 4 tg + i of the lane's row, over the lane's pieces (two halves each)
         };
+        auto mfma = [](u32x4 w, u32x4 x, f4(&c)[2]) {
+          c[0] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.x, x.y}),
+                                                    __builtin_bit_cast(h4, u2{w.x, w.y}), c[0], 0, 0, 0);
+          c[1] = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(h4, u2{x.z, x.w}),
+                                                    __builtin_bit_cast(h4, u2{w.z, w.w}), c[1], 0, 0, 0);
+        };
+        // the tokens of window w in the MFMA's layout: the two 8-value halves of
+        // the lane's piece
+        struct Tok {
+          u32x4 v[TG][2];
+        };
+        auto tokens = [&](int w) -> Tok {
+          Tok x;
 #pragma unroll
-        for (int i = 0; i < kDepth; ++i) request(i, i);
-        SI_TRACE_WAVE(0);
-        int w0 = 0;
-        Tok x = tokens(0);
+          for (int t = 0; t < TG; ++t) {
+            x.v[t][0] = xa[t * kTG + 32 * w];
+            x.v[t][1] = xa[t * kTG + 32 * w + 1];
+          }
+          return x;
+        };
+        // the products of a window of one or two matrices
+        auto window = [&](const Tok& x, u32x4 vg, u32x4 vu, Acc& ag, Acc& au, auto two) {
+          constexpr bool kTwo = decltype(two)::value;
+          u32x4 gl, gh, ul, uh;
+          i8_to_h16(vg, gl, gh);
+          if constexpr (kTwo) i8_to_h16(vu, ul, uh);
+#pragma unroll
+          for (int t = 0; t < TG; ++t) {
+            mfma(gl, x.v[t][0], ag.v[t]);
+            mfma(gh, x.v[t][1], ag.v[t]);
+            if constexpr (kTwo) {
+              mfma(ul, x.v[t][0], au.v[t]);
+              mfma(uh, x.v[t][1], au.v[t]);
+            }
+          }
+        };
+        // the whole rows, kDepth windows of them in flight: a window's registers
+        // take the request kDepth windows on as soon as it is multiplied (the
+        // scheduling barriers keep the request there, and the tokens one window
+        // ahead).  Windows past the row's end request its last unit again and
+        // are left out of the products; in the last window of a row of an odd
+        // number of 128-byte lines the tokens' units past d are zero.
+        constexpr int kDepth = kWinMax < 8 ? kWinMax : 8;
+        auto rows = [&](const u32x4* pg, const u32x4* pu, Acc& ag, Acc& au, auto two) {
+          constexpr bool kTwo = decltype(two)::value;
+          u32x4 vg[kDepth], vu[kTwo ? kDepth : 1];
+          auto request = [&](int i, int w) {
+            const int u = min(16 * w + qp, rowu - 1);
+            vg[i] = load_nt(pg + u);
+            if constexpr (kTwo) vu[i] = load_nt(pu + u);
+          };
+#pragma unroll
+          for (int i = 0; i < kDepth; ++i) request(i, i);
+          SI_TRACE_WAVE(0);
+          int w0 = 0;
+          Tok x = tokens(0);
 #pragma unroll 1
-        for (; w0 + kDepth < nwin; w0 += kDepth) {
+          for (; w0 + kDepth < nwin; w0 += kDepth) {
+#pragma unroll
+            for (int i = 0; i < kDepth; ++i) {
+              const Tok xn = tokens(w0 + i + 1);
+              window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
+              request(i, w0 + kDepth + i);
+              __builtin_amdgcn_sched_barrier(0);
+              x = xn;
+            }
+          }
 #pragma unroll
           for (int i = 0; i < kDepth; ++i) {
-            const Tok xn = tokens(w0 + i + 1);
-            window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
-            request(i, w0 + kDepth + i);
-            __builtin_amdgcn_sched_barrier(0);
+            const Tok xn = tokens(min(w0 + i + 1, nwin - 1));
+            if (w0 + i < nwin) window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
             x = xn;
           }
-        }
-#pragma unroll
-        for (int i = 0; i < kDepth; ++i) {
-          const Tok xn = tokens(min(w0 + i + 1, nwin - 1));
-          if (w0 + i < nwin) window(x, vg[i], vu[kTwo ? i : 0], ag, au, two);
-          x = xn;
-        }
-      };
-      // the lane's row's dot products, summed over the 16 pieces (every lane
-      // of the row has them)
-      auto total = [&](const Acc& acc, float(&o)[BM]) {
-#pragma unroll
-        for (int t = 0; t < BM; ++t) {
-          float v = acc.v[t >> 2][0][t & 3] + acc.v[t >> 2][1][t & 3];
-          v = dpp_add<0x124>(v);  // row_ror:4
-          v = dpp_add<0x128>(v);  // row_ror:8
-          v += __shfl_xor(v, 16, kWave);
-          o[t] = v + __shfl_xor(v, 32, kWave);
-        }
-      };
-      for (int pos = lo + kUpRows * uniform(wv); pos < hi;) {
-        const int cnt = min(kUpRows, hi - pos);
-        const uint32_t e = L.dent[pos + min(qn, cnt - 1)];  // the lane's row (a repeat of the last one past the end)
-        // rows whose W_up is requested with W_gate; the other lanes repeat one
-        // of them (no bytes of their own)
-        const bool early = gated && ((spec_ok && (e >> 31)) || no_as);
-        const uint32_t em = (uint32_t)__ballot(early && qn < cnt) & 0xfu;
-        auto row_of = [&](const u32x4* m, uint32_t mask) {
-          const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)e, __builtin_ctz(mask));
-          return m + (size_t)(((mask >> qn) & 1u ? e : f) & 0x7fffffffu) * rowu;
         };
-        const float sgv = a.sg[e & 0x7fffffffu];
-        const float suv = gated ? a.su[e & 0x7fffffffu] : 1.f;
-        Acc ag = {}, au = {};
-        const u32x4* pg = a.wg + (size_t)(e & 0x7fffffffu) * rowu;
-        if (em)
-          rows(pg, row_of(a.wu, em), ag, au, std::true_type{});
-        else
-          rows(pg, pg, ag, au, std::false_type{});
-        float g[BM], u[BM];
-        total(ag, g);
-        total(au, u);
-        bool any = false;
+        // the lane's row's dot products, summed over the 16 pieces (every lane
+        // of the row has them)
+        auto total = [&](const Acc& acc, float(&o)[BM]) {
 #pragma unroll
-        for (int t = 0; t < BM; ++t) {
-          g[t] = fmaxf(g[t] * sgv, 0.f);
-          any |= g[t] > 0.f;
-        }
-        // rows whose gate value asks for W_up only now (actual sparsity)
-        const uint32_t lm = (uint32_t)__ballot(any && gated && !early && qn < cnt) & 0xfu;
-        if (lm) {
-          Acc al = {}, unused;
-          rows(row_of(a.wu, lm), pg, al, unused, std::false_type{});
-          float v[BM];
-          total(al, v);
+          for (int t = 0; t < BM; ++t) {
+            float v = acc.v[t >> 2][0][t & 3] + acc.v[t >> 2][1][t & 3];
+            v = dpp_add<0x124>(v);  // row_ror:4
+            v = dpp_add<0x128>(v);  // row_ror:8
+            v += __shfl_xor(v, 16, kWave);
+            o[t] = v + __shfl_xor(v, 32, kWave);
+          }
+        };
+        for (int pos = lo + kUpRows * uniform(wv); pos < hi;) {
+          const int cnt = min(kUpRows, hi - pos);
+          const uint32_t e = L.dent[pos + min(qn, cnt - 1)];  // the lane's row (a repeat of the last one past the end)
+          // rows whose W_up is requested with W_gate; the other lanes repeat one
+          // of them (no bytes of their own)
+          const bool early = gated && ((spec_ok && (e >> 31)) || no_as);
+          const uint32_t em = (uint32_t)__ballot(early && qn < cnt) & 0xfu;
+          auto row_of = [&](const u32x4* m, uint32_t mask) {
+            const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)e, __builtin_ctz(mask));
+            return m + (size_t)(((mask >> qn) & 1u ? e : f) & 0x7fffffffu) * rowu;
+          };
+          const float sgv = a.sg[e & 0x7fffffffu];
+          const float suv = gated ? a.su[e & 0x7fffffffu] : 1.f;
+          Acc ag = {}, au = {};
+          const u32x4* pg = a.wg + (size_t)(e & 0x7fffffffu) * rowu;
+          if (em)
+            rows(pg, row_of(a.wu, em), ag, au, std::true_type{});
+          else
+            rows(pg, pg, ag, au, std::false_type{});
+          float g[BM], u[BM];
+          total(ag, g);
+          total(au, u);
+          bool any = false;
 #pragma unroll
-          for (int t = 0; t < BM; ++t) u[t] = (lm >> qn) & 1u ? v[t] : u[t];
-        }
-        const bool have_u = ((em | lm) >> qn) & 1u;
-        float hv = 0.f;  // lane 4 t + n: token t of row n
+          for (int t = 0; t < BM; ++t) {
+            g[t] = fmaxf(g[t] * sgv, 0.f);
+            any |= g[t] > 0.f;
+          }
+          // rows whose gate value asks for W_up only now (actual sparsity)
+          const uint32_t lm = (uint32_t)__ballot(any && gated && !early && qn < cnt) & 0xfu;
+          if (lm) {
+            Acc al = {}, unused;
+            rows(row_of(a.wu, lm), pg, al, unused, std::false_type{});
+            float v[BM];
+            total(al, v);
 #pragma unroll
-        for (int t = 0; t < BM; ++t)
-          hv = qp == t ? g[t] * (!gated ? 1.f : have_u ? u[t] * suv : 0.f) : hv;
-        if (qn < cnt && qp < b)
-          st_agent64(&a.h3e[(size_t)(e & 0x7fffffffu) * b + qp], tagged(tag, __float_as_uint(hv)));
-        n_up += __popc(em) + __popc(lm);
-        int nxt = hi;
-        if (lo + kUpRows * kOW < hi) {
-          if (lane == 0) nxt = atomicAdd(&L.gpos, kUpRows);
-          nxt = __builtin_amdgcn_readfirstlane(nxt);
+            for (int t = 0; t < BM; ++t) u[t] = (lm >> qn) & 1u ? v[t] : u[t];
+          }
+          const bool have_u = ((em | lm) >> qn) & 1u;
+          float hv = 0.f;  // lane 4 t + n: token t of row n
+#pragma unroll
+          for (int t = 0; t < BM; ++t)
+            hv = qp == t ? g[t] * (!gated ? 1.f : have_u ? u[t] * suv : 0.f) : hv;
+          if (qn < cnt && qp < b)
+            st_agent64(&a.h3e[(size_t)(e & 0x7fffffffu) * b + qp], tagged(tag, __float_as_uint(hv)));
+          n_up += __popc(em) + __popc(lm);
+          int nxt = hi;
+          if (lo + kUpRows * kOW < hi) {
+            if (lane == 0) nxt = atomicAdd(&L.gpos, kUpRows);
+            nxt = __builtin_amdgcn_readfirstlane(nxt);
+          }
+          pos = nxt;
         }
-        pos = nxt;
       }
-    } else {
+    }
+    if (!mfma_up) {
       // one token: a wave announces (LDS counter) that its first row's
       // requests are out, so that the waves without a row can queue their
       // W_down^T pieces behind them
@@ -1264,7 +1278,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
             load_row<NU8>(a.wu + (size_t)urow * U8, U8, lane, vu);
             announce();
             const float sgv = a.sg[urow], suv = a.su[urow];
-            row_dots_i8<BM, NU, true>(vg, vu, L.xs, U8, lane, g, u);
+            row_dots_i8<BM, NU, XP, true>(vg, vu, L.xs, U8, lane, g, u);
 #pragma unroll
             for (int t = 0; t < BM; ++t) {
               g[t] *= sgv;
@@ -1276,7 +1290,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
             load_row<NU8>(a.wg + (size_t)urow * U8, U8, lane, vg);
             announce();
             const float sgv = a.sg[urow];
-            row_dots_i8<BM, NU, false>(vg, vg, L.xs, U8, lane, g, u);
+            row_dots_i8<BM, NU, XP, false>(vg, vg, L.xs, U8, lane, g, u);
             bool any = false;
 #pragma unroll
             for (int t = 0; t < BM; ++t) {
@@ -1290,7 +1304,7 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
               if constexpr (BM >= 2) asm volatile("" ::: "memory");
               const float suv = a.su[urow];
               float unused[BM];
-              row_dots_i8<BM, NU, false>(vu, vu, L.xs, U8, lane, u, unused);
+              row_dots_i8<BM, NU, XP, false>(vu, vu, L.xs, U8, lane, u, unused);
 #pragma unroll
               for (int t = 0; t < BM; ++t) u[t] *= suv;
             } else {

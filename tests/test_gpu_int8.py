@@ -272,6 +272,32 @@ def test_int8_tokens_large_shares(d, R, b, gated, flags):
     check(c, mask, y, cnt, flags)
 
 
+@pytest.mark.parametrize("d,b,gated,flags", [(512, 3, True, 0), (512, 4, False, 0), (1152, 4, True, si.SI_NO_AS),
+                                             (2176, 3, False, 0), (4224, 4, True, si.SI_NO_SPECULATION),
+                                             (4224, 3, True, 0), (8192, 3, True, 0)])
+def test_int8_tokens_small_shares(d, b, gated, flags):
+    """3-4 tokens on both sides of the line between rows dealt one to a wave
+    (up to 8 rows of W_gate and W_up together) and four at a time: every
+    share of 0 to 16 rows per block, the blocks of one group sharing 0 to 16
+    times their number (and one row more, so that shares within a group
+    differ)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T, R = (d + 511) // 512, 17
+    groups, rows = cus // T, T * R
+    k = groups * rows
+    rng = np.random.default_rng(100 * d + b)
+    mask = np.zeros((groups, rows), np.uint8)
+    for g in range(groups):
+        mask[g, rng.permutation(rows)[: min(g % 17 * T + (g // 17) % 2, rows)]] = 1
+    mask = mask.reshape(-1)
+    c = I8Case(rand_bits(rng, (k, d)), rand_bits(rng, (k, d)) if gated else None, rand_bits(rng, (d, k)),
+               rand_bits(rng, (b, d)), max_batch=b)
+    assert si._lib.load().si_single_launch(k, d, b) == 1
+    y, cnt = c.layer.sparse_mlp(to_dev(c.x), torch.from_numpy(mask).to(DEV), flags=flags, counters=True)
+    torch.cuda.synchronize()
+    check(c, mask, y, cnt, flags)
+
+
 @pytest.mark.parametrize("k,d,gated", [(9000, 8192, True), (40000, 2048, True), (20000, 4096, False)])
 def test_int8_one_token_large_groups(k, d, gated):
     """One token with groups of more than 512 rows (T = ceil(d / 512) blocks
