@@ -124,10 +124,6 @@ inline int units_per_lane(int d) {
 // Batch bucket of the kernel: the smallest of 1, 2, 4, 8 that holds b.
 inline int batch_bucket(int b) { return b <= 1 ? 1 : b <= 2 ? 2 : b <= 4 ? 4 : 8; }
 
-// Per-block work counts -> counters[3] = {n_gate, n_up, n_down}.
-hipError_t launch_sum_counts(const int32_t* counts, int slots, const int32_t* n_active, int k, int32_t* counters,
-                             hipStream_t s);
-
 #define SI_NU_DISPATCH(BM, CALL)   \
   switch (units_per_lane(d)) {     \
     case 1: return CALL(BM, 1);    \

@@ -44,9 +44,7 @@ struct WsLayout {
   size_t idx;     // int32 [k] kept rows (when the caller gives none)
   size_t mask;    // uint8 [k] mask (when the caller gives none)
   size_t upflag;  // uint8 [k] 1 where the W_up row was read
-  size_t lmask;   // uint64 [groups][4] single-kernel kept / confident masks
   size_t zflag;   // uint64 [64] single-kernel "tile of y zeroed" flags
-  size_t spare;   // uint64 [kMaxLayerBlocks], not used (callers' workspaces keep their size)
   size_t opub;    // uint64 [kMaxLayerBlocks][kOwnPubStride] row-owning kernel: masks and count per block
   size_t h3;      // float [k][b] h3 per row (valid on kept rows)
   size_t h3e;     // uint64 [groups][64][b] single-kernel h3 exchange words
@@ -70,10 +68,8 @@ __host__ __device__ inline WsLayout ws_layout(int k, int b) {
   L.idx = L.counts + align256((size_t)count_slots(k) * 2 * sizeof(int32_t));
   L.mask = L.idx + align256((size_t)k * sizeof(int32_t));
   L.upflag = L.mask + align256((size_t)k);
-  L.lmask = L.upflag + align256((size_t)k);
-  L.zflag = L.lmask + align256(groups * 4 * sizeof(uint64_t));
-  L.spare = L.zflag + align256(64 * sizeof(uint64_t));
-  L.opub = L.spare + align256(kMaxLayerBlocks * sizeof(uint64_t));
+  L.zflag = L.upflag + align256((size_t)k);
+  L.opub = L.zflag + align256(64 * sizeof(uint64_t));
   L.h3 = L.opub + align256((size_t)kMaxLayerBlocks * kOwnPubStride * sizeof(uint64_t));
   L.h3e = L.h3 + align256((size_t)k * b * sizeof(float));
   L.total = L.h3e + align256(groups * kRowGroup * (size_t)b * sizeof(uint64_t));

@@ -94,6 +94,10 @@ bool owned_supported(int k, int d, int b);
 bool list_supported(int k, int d, int b);
 hipError_t launch_owned(const LayerCall& c, hipStream_t s);
 
+// Per-block work counts -> counters[3] = {n_gate, n_up, n_down}.
+hipError_t launch_sum_counts(const int32_t* counts, int slots, const int32_t* n_active, int k, int32_t* counters,
+                             hipStream_t s);
+
 // Per-row h3 of the last MLP call made with workspace `ws` -> out[k][b]
 // (kept rows of `mask`; 0 elsewhere; NaN where the call left no value).
 hipError_t launch_read_h3(const void* ws, int k, int b, const uint8_t* mask, float* out, hipStream_t s);
