@@ -106,7 +106,7 @@ constexpr int kODN1Wide = 12;
 static_assert(kODN1 < kWave && kODN1Int8 < kWave && kODN1Wide < kWave, "a wave's last lane polls the tile's zero flag");
 static_assert(kODN * kMaxB <= kWave, "a wave polls the h3 words of its pieces, one lane per (piece, token)");
 
-// The down-projection on the matrix cores (4-8 tokens; INT8 pieces are
+// The down-projection on the matrix cores (3-8 tokens; INT8 pieces are
 // turned into fp16, exactly, on their way into LDS): the group's rows in
 // chunks of 32 (the K of one 16x16x32 fp16 MFMA), the tile's
 // 512 columns split over the 8 waves (64 each, four 16-column blocks), the
@@ -1080,8 +1080,8 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
         // MFMA's layout as it comes; the tokens come from LDS in the same
         // layout, once for W_gate and W_up.  On the vector ALU (a row pair per
         // wave, converted and multiplied with every token in turn) the phase
-        // was issue bound: the 8-token 7B call took 46.4 us, with this 35.9 (gate/up
-        // done at 23.8 us, now 15-18, of which the 45 MB of rows take 8).  fp16
+        // was issue bound: the 8-token 7B call took 46.4 us, with this 35.9 (in the
+        // mask call the 51 MB of rows end 7-10 us after the group list).  fp16
         // rows stay on the vector ALU: their phase is bound by the rows'
         // bytes, and whole rows requested 1 KB at a time stream better than the
         // 4 x 256 bytes here (4 tokens 24.2 us, this way 26.4; 8 tokens 41.7 and
@@ -1991,9 +1991,10 @@ bool owned_supported(int k, int d, int b) {
   return tiles * nsub <= kMaxPairs && tiles * R <= kMaxChunkRows;
 }
 
-// The list form: each block's share as above, the list's slices (over all
-// whole groups) in the LDS list; k as far as the other forms where the whole
-// groups cover the grid.
+// The list form: the list's slices (over all whole groups) in the LDS list.
+// It has no rows of a block's own: the bound on them only keeps its range the
+// one that si_single_launch answers for (calls beyond take two launches in
+// every form).
 bool list_supported(int k, int d, int b) {
   const int P = owned_blocks_for(d, b);
   const int tiles = (d + kTile - 1) / kTile;

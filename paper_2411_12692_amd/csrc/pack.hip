@@ -93,7 +93,7 @@ __device__ inline int quantize_one(float w, float s, float inv) {
 // values is read once, 16 bytes a lane, all of it requested together, and kept
 // in registers between the maximum and the rounding (NV = 0: rows longer
 // than that, read twice).  (One value a lane, two reads of the row and a division each:
-// 11008 x 4096 in 92.7 us = 1.46 TB/s; now 27.2 us = 5.0 TB/s.)
+// 11008 x 4096 in 92.7 us = 1.46 TB/s; now 26.5-29.8 us = 4.5-5.1 TB/s.)
 template <int NT, int NV>
 __global__ __launch_bounds__(NT) void k_quantize_rows(const uint16_t* __restrict__ w, int n,
                                                        int8_t* __restrict__ q, float* __restrict__ scale) {
@@ -272,7 +272,7 @@ hipError_t launch_pack_signs_i8(const int8_t* w_gate, int k, int d, uint32_t* si
 hipError_t launch_quantize_rows(const uint16_t* w, int rows, int n, int8_t* q, float* scale, hipStream_t s) {
   // rows of up to 4096 values: 256 threads with 2 vectors of 8 each; longer
   // ones 512 threads with 3 (12288 values) or 4 (with 256 threads and 6 vectors,
-  // 4096 x 11008 took 41.9 us, so 31.4: too few waves to cover the reads)
+  // 4096 x 11008 took 41.9 us, so 31.0-33.2: too few waves to cover the reads)
   const int nv = n >> 3;
   if (nv <= 512)
     k_quantize_rows<256, 2><<<rows, 256, 0, s>>>(w, n, q, scale);

@@ -60,9 +60,10 @@ def test_quantize_lengths(n):
 
 
 def test_quantize_every_quotient_near_a_half():
-    """Every pair of an fp16 value and a row maximum in two binades whose
-    quotient comes near a half of the scale: the product with the inverse
-    must never decide a tie differently from the division."""
+    """Every fp16 value from 1/8 up to the row's maximum, over every seventh
+    fp16 maximum from 1 to 2 (a binade has every fraction of the quotients):
+    the product with the inverse must never decide a tie differently from the
+    division."""
     maxima = np.arange(1024, 2048, 7).astype(np.uint16) | np.uint16(0x3800)
     vals = np.arange(0x3000, 0x4000, dtype=np.uint16)
     rows = np.broadcast_to(vals, (maxima.size, vals.size)).copy().view(np.float16)
