@@ -1047,8 +1047,11 @@ __global__ __launch_bounds__(kOT) void k_owned(OwnedArgs a) {
     // win (2048 x 5632, 3 tokens, s = 0.9, six rows: 12.55, else 13.87); with 5-8
     // tokens they do at every share (s = 0.993: 17.3, else 17.7).  Dealing them
     // fewer than four rows a wave was slower at every share (7B, 4 tokens, s =
-    // 0.97: 16.35 -> 18.16).
-    const bool mfma_up = kMfmaUp && (BM > 4 || (gated ? 2 : 1) * (hi - lo) > kOW);
+    // 0.97: 16.35 -> 18.16).  Rows of 513-1024 values are one request each, and
+    // the line lies at 10 rows (1024 x 6144, mask of 4 tokens, s = 0.9, 8.3 rows:
+    // 13.26 -> 12.68; at 11.5 rows the matrix cores' 13.57 against 13.80).
+    const int few = NU == 2 ? kOW + 2 : gated ? kOW / 2 : kOW;
+    const bool mfma_up = kMfmaUp && (BM > 4 || hi - lo > few);
     if (tid == 0) {
       L.gpos = lo + (mfma_up ? kUpRows : up_rows) * kOW;
       L.dpos = 0;

@@ -272,12 +272,14 @@ def test_int8_tokens_large_shares(d, R, b, gated, flags):
     check(c, mask, y, cnt, flags)
 
 
-@pytest.mark.parametrize("d,b,gated,flags", [(512, 3, True, 0), (512, 4, False, 0), (1152, 4, True, si.SI_NO_AS),
+@pytest.mark.parametrize("d,b,gated,flags", [(512, 3, True, 0), (512, 4, False, 0), (640, 3, False, 0),
+                                             (1024, 4, True, 0), (1152, 4, True, si.SI_NO_AS),
                                              (2176, 3, False, 0), (4224, 4, True, si.SI_NO_SPECULATION),
                                              (4224, 3, True, 0), (8192, 3, True, 0)])
 def test_int8_tokens_small_shares(d, b, gated, flags):
     """3-4 tokens on both sides of the line between rows dealt one to a wave
-    (up to 8 rows of W_gate and W_up together) and four at a time: every
+    (up to 8 rows of W_gate and W_up together, at d = 640 and 1024 up
+    to 10 rows) and four at a time: every
     share of 0 to 16 rows per block, the blocks of one group sharing 0 to 16
     times their number (and one row more, so that shares within a group
     differ)."""
